@@ -190,12 +190,6 @@ typedef __attribute__((address_space(4))) int32_t cint32_t;   // read-only (scal
 // itself (wait_loads_and_sync), before the barrier that publishes a stage.
 // The compiler's own vector-memory waits stay correct: loads return in order,
 // so loads it does not know of can only make its waits longer.
-// Buffer descriptor words: base[31:0]; base[47:32] (stride 0); byte size;
-// raw-buffer flags.
-__device__ __forceinline__ i32x4 buf_desc(const void* base, uint32_t bytes) {
-    const uint64_t b = reinterpret_cast<uint64_t>(base);
-    return i32x4{(int)(uint32_t)b, (int)((uint32_t)(b >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     return (uint32_t)(uintptr_t)(lds_ptr_t)p;
 }
@@ -219,25 +213,28 @@ __device__ __forceinline__ i32x4 uniform4(const i32x4 d) {
     return i32x4{__builtin_amdgcn_readfirstlane(d[0]), __builtin_amdgcn_readfirstlane(d[1]),
                  __builtin_amdgcn_readfirstlane(d[2]), __builtin_amdgcn_readfirstlane(d[3])};
 }
-// Four 1 KB blocks at dst + 1024 k from voff + 1024 k (k = 0 .. 3): the
+// Four 1 KB blocks at dst + 1024 k from voff + soff + 1024 k (k = 0 .. 3): the
 // instruction's immediate offset moves both the memory and the LDS address.
-__device__ __forceinline__ void dma16x4(const i32x4 desc, uint32_t dst, uint32_t voff) {
+__device__ __forceinline__ void dma16x4(const i32x4 desc, uint32_t dst, uint32_t voff, uint32_t soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, %2, 0 offen lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, 0 offen offset:2048 lds\n\t"
-                 "buffer_load_dwordx4 %1, %2, 0 offen offset:3072 lds"
-                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)) : "memory", "m0");
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:3072 lds"
+                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)),
+                    "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory", "m0");
 }
-// one 1 KB block with a scalar offset added to the memory address
+// one 1 KB block
 __device__ __forceinline__ void dma16s(const i32x4 desc, uint32_t dst, uint32_t voff, uint32_t soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)),
                     "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory", "m0");
 }
-__device__ __forceinline__ void dma4(const i32x4 desc, uint32_t dst, uint32_t voff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)) : "memory", "m0");
+// 256 bytes, one dword a lane
+__device__ __forceinline__ void dma4(const i32x4 desc, uint32_t dst, uint32_t voff, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)),
+                    "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory", "m0");
 }
 
 // f(std::integral_constant<int, I>{}) for I = 0 .. N-1, in order
@@ -366,14 +363,9 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     }
 
     // Operands in device group order: the group-g main-plane tile of X rows
-    // m0.. is xrows * 64 contiguous bytes at (g M + m0) 64, that of block row
-    // br 8 KB at (g N + 128 br) 64, and R block p is 8 KB.  These loads
-    // go through a resource spanning exactly that tile (offsets in the vector
-    // operand only), so X rows past xrows fail the range check and read zero;
-    // the tail-plane loads use the whole-operand resource with such rows moved
-    // past its end.
-    const uint32_t xrows = (uint32_t)min(TM, M - m0);
-    const uint32_t xbytes = xrows * (uint32_t)kRow;
+    // m0.. is contiguous at (g M + m0) 64, its tails at (g M + m0) 32 of the
+    // tail plane, that of block row br 8 KB at (g N + 128 br) 64, and R block
+    // p is 8 KB.
     const uint32_t tail0 = (uint32_t)G * (uint32_t)M * (uint32_t)kRow;
 
     // CSR walks of the tile's NBR block rows, from the first entry at or after
@@ -392,6 +384,11 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             rp[b] = rowptr[br[b]];
             re[b] = rowptr[br[b] + 1];
             while (rp[b] < re[b] && res_kb[rp[b]] < gb) ++rp[b];
+            if constexpr (SPLIT) {                         // the entries of this split only
+                int e = rp[b];
+                while (e < re[b] && res_kb[e] < ge) ++e;
+                re[b] = e;
+            }
             if (rp[b] < re[b]) nk[b] = res_kb[rp[b]];
         }
     }
@@ -420,8 +417,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // row 16 b + l / 4 is (l / 8) % 4 for every b, so block k is 1024 k on)
     const uint32_t vt = (uint32_t)(64 * ld + (lane >> 2)) * kRow + (((lane & 3) ^ ((lane >> 3) & 3)) << 4);
     const uint32_t vr = (uint32_t)(64 * (ld & 1) + (lane >> 2)) * kRow + (((lane & 3) ^ ((lane >> 3) & 3)) << 4);
-    // tail blocks: quarter pair tq[k], rows trow[k] + l (lane offsets past the
-    // end for rows from M on)
+    // tail blocks: quarter pair tq[k], rows trow[k] + l
     constexpr int kRowBlocks = TM / 64;                     // 64-row blocks of the tail tile per quarter pair
     int tq[2], trow[2];
     uint32_t vtl[2];
@@ -430,92 +426,62 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
         const int b = 2 * ld + k;
         tq[k] = b / kRowBlocks;
         trow[k] = 64 * (b % kRowBlocks);
-        vtl[k] = ((uint32_t)(trow[k] + lane) * 32u + 16u * (uint32_t)tq[k]) | (m0 + trow[k] + lane < M ? 0u : kPastEnd);
+        vtl[k] = (uint32_t)(trow[k] + lane) * 32u + 16u * (uint32_t)tq[k];
     }
 
-    // Loads of group g into `slot` (issued by the loaders right after the
-    // barrier inside the dense pass of group g - 2; past the last group they
-    // read nothing: zero-size resources, offsets past the end).  p[b] is block
-    // row b's residual block at g (-1: none).
-    struct Plan {
-        i32x4 xr, wr, sc;                    // resources
-        uint32_t x, w, s, xt[2];             // LDS destinations
-        uint32_t xto[2];                     // tail-plane block offsets (uniform; past the end: read nothing)
-        bool has_s;
-    };
-    auto plan = [&](int g, int slot, int (&p)[NBR]) -> Plan {
-        const bool live = g < ge;
-        const int gl = live ? g : 0;
-        Plan P;
-        P.xr = buf_desc(a.Xq + piece_offset(M, m0, gl), live ? xbytes : 0u);
-        P.wr = buf_desc(a.Wq + piece_offset(N, kTB * br[lbr], gl), live ? (uint32_t)kTile : 0u);
-        P.x = lds_addr(&L.x[slot][(4 * ld) * 1024]);
-        P.w = lds_addr(&L.w[slot][(4 * ld) * 1024]);
+    // Loads of the next group in turn into `slot` (issued by the loaders right
+    // after the barrier inside the dense pass two groups earlier), through the
+    // whole-operand resources: scalar offsets that step from group to group, so
+    // a group costs a handful of scalar instructions.  (About a hundred --
+    // resources built afresh for every group -- ran in both waves of a SIMD at
+    // the same time, with nothing to cover them: K = N = M = 4096 50.7 -> 49.2
+    // us, 14336 -> 4096 141.9 -> 136.3, on 128 x 128 tiles at M = 1024 73.5 ->
+    // 69.7.)  No address needs a guard: past the last group W, its scales and
+    // the tails run off their operands, which reads nothing (offsets stay below
+    // 2^32), X is sent past its end, and a split's last two groups load those of
+    // the next split.  X rows past M are other bytes of Xq (rows of the next
+    // group, or of the tail plane): finite codes whose sums are not stored.
+    uint32_t xso = ((uint32_t)gb * (uint32_t)M + (uint32_t)m0) * kRow, xto = tail0 + xso / 2;
+    uint32_t wso = ((uint32_t)gb * (uint32_t)N + (uint32_t)(kTB * br[lbr])) * kRow;
+    const bool has_s = !RAW && ld < NBR;
+    uint32_t sso = ((uint32_t)gb * (uint32_t)N + (uint32_t)(kTB * br[ld < NBR ? ld : 0])) * 2u;
+    const uint32_t xend = (uint32_t)G * (uint32_t)M * kRow;                     // of the main plane
+    auto issue = [&](int slot) {
+        if (!loader) return;
+        dma16x4(a.rx, lds_addr(&L.x[slot][(4 * ld) * 1024]), vt, xso < xend ? xso : kPastEnd);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            P.xt[k] = lds_addr(&L.xt[slot][tq[k]][trow[k] * 16]);
-            P.xto[k] = live ? tail0 + ((uint32_t)gl * (uint32_t)M + (uint32_t)m0) * 32u : kPastEnd;
-        }
+        for (int k = 0; k < 2; ++k) dma16s(a.rx, lds_addr(&L.xt[slot][tq[k]][trow[k] * 16]), vtl[k], xto);
+        dma16x4(a.rw, lds_addr(&L.w[slot][(4 * ld) * 1024]), vr, wso);            // rows of block row lbr
+        if (has_s) dma4(a.rsw, lds_addr(&L.sw[slot][64 * ld]), (uint32_t)lane * 4, sso);
+        xso += (uint32_t)M * kRow;
+        xto += (uint32_t)M * (kRow / 2);
+        wso += (uint32_t)N * kRow;
+        sso += (uint32_t)N * 2u;
+    };
+    // block row b's residual block at group g (-1: none); groups are asked for in order
+    auto next_blocks = [&](int g, int (&p)[NBR]) {
 #pragma unroll
         for (int b = 0; b < NBR; ++b) {
             p[b] = -1;
-            if (live && nk[b] == g) {
+            if (nk[b] == g) {
                 p[b] = rp[b]++;
                 nk[b] = rp[b] < re[b] ? res_kb[rp[b]] : 0x7fffffff;
             }
         }
-        P.has_s = false;
-        P.sc = buf_desc(a.Wq, 0u);
-        P.s = 0;
-        if constexpr (!RAW) {
-            if (live && ld < NBR) {
-                P.has_s = true;
-                P.sc = buf_desc(a.s_w + wscale_index(N, kTB * br[ld], g), kTB * 2);
-                P.s = lds_addr(&L.sw[slot][64 * ld]);
-            }
-        }
-        return P;
     };
-    // Residual loads of group g (blocks p) into residual slot rs, issued one
+    // Residual loads of a group (blocks p) into residual slot rs, issued one
     // group ahead.
-    struct RPlan {
-        i32x4 rr, sc;
-        uint32_t r, s;
-        bool has_r, has_s;
-    };
-    auto rplan = [&](int rs, const int (&p)[NBR]) -> RPlan {
-        RPlan P;
+    auto issue_r = [&](int rs, const int (&p)[NBR]) {
+        if (!loader) return;
         const int pr = (NBR == 2 && lbr == 1) ? p[NBR - 1] : p[0];
-        P.has_r = pr >= 0;
-        P.rr = buf_desc(a.Rq + (int64_t)(pr >= 0 ? pr : 0) * kTile, (uint32_t)kTile);
-        P.r = lds_addr(&L.r[rs][lbr][(4 * (ld & 1)) * 1024]);
-        P.has_s = false;
-        P.sc = buf_desc(a.Wq, 0u);
-        P.s = 0;
+        if (pr >= 0)
+            dma16x4(a.rr, lds_addr(&L.r[rs][lbr][(4 * (ld & 1)) * 1024]), vr, (uint32_t)pr * (uint32_t)kTile);
         if constexpr (!RAW) {
             const int sb = ld - NBR;
             const int ps = (NBR == 2 && sb == 1) ? p[NBR - 1] : p[0];
-            if (sb >= 0 && sb < NBR && ps >= 0) {
-                P.has_s = true;
-                P.sc = buf_desc(a.s_r + (int64_t)ps * kTB, kTB * 2);
-                P.s = lds_addr(L.sr[rs][sb]);
-            }
+            if (sb >= 0 && sb < NBR && ps >= 0)
+                dma4(a.rsr, lds_addr(L.sr[rs][sb]), (uint32_t)lane * 4, (uint32_t)ps * (kTB * 2u));
         }
-        return P;
-    };
-    // the loads of a plan (loaders only; outside any MFMA block)
-    auto issue = [&](const Plan& P) {
-        if (!loader) return;
-        dma16x4(P.xr, P.x, vt);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) dma16s(a.rx, P.xt[k], vtl[k], P.xto[k]);
-        dma16x4(P.wr, P.w, vr);                            // rows of block row lbr
-        if (P.has_s) dma4(P.sc, P.s, (uint32_t)lane * 4);
-    };
-    auto issue_r = [&](const RPlan& P) {
-        if (!loader) return;
-        if (P.has_r) dma16x4(P.rr, P.r, vr);
-        if (P.has_s) dma4(P.sc, P.s, (uint32_t)lane * 4);
     };
 
     f32x4 acc[WM][WN];
@@ -590,14 +556,14 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // (MFMAs of the first half still running: the compiler places the wait
     // states of their results across the blocks of the load issue) it waits
     // for the loads in flight, meets the other waves (which frees the slots of
-    // the previous group), has the loaders issue the loads of plans P and RP
-    // and reads the next group's operands ahead into H.  A residual pass
+    // the previous group), has the loaders issue the loads of the group after next and of the next
+    // group's residual blocks rp_next, and reads the next group's operands ahead into H.  A residual pass
     // multiplies the sub-tiles in the bit set RES (those of one block row) with
     // the R fragments of that block row from residual slot RS.  The fp32 path
     // accumulates scale x (group sum / 64); the factor 64 is applied once, in
     // the final epilogue (exact).
     constexpr int kSync = WM / 2;
-    auto phase = [&](auto slot_c, auto res_c, Ahead& H, int rs, const Plan& P, const RPlan& RP) {
+    auto phase = [&](auto slot_c, auto res_c, Ahead& H, int rs, const int (&rp_next)[NBR]) {
         constexpr int SL = decltype(slot_c)::value, SNEXT = SL == kStages - 1 ? 0 : SL + 1;
         constexpr int RES = decltype(res_c)::value;
         constexpr bool DENSE = RES == 0;
@@ -626,7 +592,11 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
         auto a_row = [&](auto ic) -> i32x8 {
             constexpr int i = decltype(ic)::value;
             if constexpr (DENSE && i == 0) return act_operand(H.a0, H.a0t);
-            else return act_operand(a_main(SL, i), a_tail(SL, i));
+            else {
+                const i32x8 av = act_operand(a_main(SL, i), a_tail(SL, i));
+                asm volatile("");       // keeps two rows' tail reads apart (merged, they need register moves)
+                return av;
+            }
         };
         auto mfma_row = [&](auto ic, const i32x8 av) {
             constexpr int i = decltype(ic)::value;
@@ -680,8 +650,8 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             }
             if constexpr (DENSE && i == kSync - 1) {
                 wait_loads_and_sync();      // the only loads in flight are those issued one group ago
-                issue(P);
-                issue_r(RP);
+                issue((SL + 2) % kStages);
+                issue_r(rs ^ 1, rp_next);
                 read_ahead(SNEXT, H);
             }
             av = an;
@@ -694,15 +664,16 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // residual blocks of the current group and of the groups one and two
     // ahead (-1: none), per block row
     int p_cur[NBR], p_next[NBR], p_new[NBR];
-    issue(plan(gb, 0, p_cur));
-    issue_r(rplan(gb & 1, p_cur));
-    const Plan P1 = plan(gb + 1, 1, p_next);
-    issue(P1);
+    next_blocks(gb, p_cur);
+    issue(0);
+    issue_r(gb & 1, p_cur);
+    next_blocks(gb + 1, p_next);
+    issue(1);
     constexpr int kBR0 = (1 << kCPerBR) - 1;                // sub-tiles of block row 0
     // group gb (and its residual tiles) have landed once no more than the
     // loads of group gb + 1 (ten, plus its weight scales) are in flight; the
     // barrier inside gb's dense pass waits for the rest
-    wait_vm_and_sync(loader ? 10 + (P1.has_s ? 1 : 0) : 0);
+    wait_vm_and_sync(loader ? 10 + (has_s ? 1 : 0) : 0);
     Ahead H;
     read_ahead(0, H);
     // Group g (ring slot SL, known at compile time: the loop below is unrolled
@@ -716,14 +687,12 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // variants of the dense code: one code path per group keeps the
     // accumulators in fixed registers.)
     auto step = [&](auto slot_c, int g) {
-        constexpr int SL = decltype(slot_c)::value, SFREE = (SL + 2) % kStages;
-        const Plan P = plan(g + 2, SFREE, p_new);
-        const RPlan RP = rplan((g + 1) & 1, p_next);
+        next_blocks(g + 2, p_new);
         const int rs = g & 1;
-        phase(slot_c, std::integral_constant<int, 0>{}, H, rs, P, RP);
-        if (p_cur[0] >= 0) phase(slot_c, std::integral_constant<int, kBR0>{}, H, rs, P, RP);
+        phase(slot_c, std::integral_constant<int, 0>{}, H, rs, p_next);
+        if (p_cur[0] >= 0) phase(slot_c, std::integral_constant<int, kBR0>{}, H, rs, p_next);
         if constexpr (NBR == 2)
-            if (p_cur[1] >= 0) phase(slot_c, std::integral_constant<int, kBR0 << kCPerBR>{}, H, rs, P, RP);
+            if (p_cur[1] >= 0) phase(slot_c, std::integral_constant<int, kBR0 << kCPerBR>{}, H, rs, p_next);
 #pragma unroll
         for (int b = 0; b < NBR; ++b) {
             p_cur[b] = p_next[b];
@@ -1531,7 +1500,8 @@ static bool large_tiles_fit(int M, int N) {
     return kLargeRoundPct * rl < kSmallRoundPct * rs;
 }
 
-// Buffer resource words (as buf_desc), built on the host.
+// Buffer resource words, built on the host: base[31:0]; base[47:32] (stride
+// 0); byte size; raw-buffer flags.
 static i32x4 host_buf_desc(const void* base, uint32_t bytes) {
     const uint64_t b = reinterpret_cast<uint64_t>(base);
     return i32x4{(int)(uint32_t)b, (int)((uint32_t)(b >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
