@@ -247,7 +247,7 @@ mq_status mq_quantize_act8(const void* X, int M, int K, int ldx,
  * W4A8 layer: as mq_fused_gemm (same weights, residual blocks, epilogue of
  * Section 3 Eq. (4) and Eq. (2)) with INT8 activation codes Xq8 (layout of
  * mq_quantize_act8).  Exact integer group sums (|sum| <= 127 * 7 * 128).
- * Every M runs on the streaming kernels (no workspace).
+ * No workspace at any M.
  */
 mq_status mq_fused_gemm_a8(int M, int N, int K,
                            const uint8_t* Xq8, const void* s_x,

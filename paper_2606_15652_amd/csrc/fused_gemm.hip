@@ -224,6 +224,14 @@ __device__ __forceinline__ void dma16x4(const i32x4 desc, uint32_t dst, uint32_t
                  :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)),
                     "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory", "m0");
 }
+// two 1 KB blocks
+__device__ __forceinline__ void dma16x2(const i32x4 desc, uint32_t dst, uint32_t voff, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %2, %3 offen offset:1024 lds"
+                 :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(voff), "s"(uniform4(desc)),
+                    "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory", "m0");
+}
 // one 1 KB block
 __device__ __forceinline__ void dma16s(const i32x4 desc, uint32_t dst, uint32_t voff, uint32_t soff) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
@@ -284,10 +292,17 @@ struct TileShape {
     static constexpr int kTN = 64 * WAVES_N;
     static constexpr int kBlockRows = kTN / kTB;          // residual block rows per tile
     static constexpr int kPerCU = kWaves == 4 ? 2 : 1;
-    static_assert(kTM / 16 == 2 * kWaves && kTN / 16 == 2 * kWaves, "two 1 KB load blocks per wave and operand");
 };
 
-template <int WMB, int WAVES_N, bool RAW, bool SPLIT>
+// A8 (the W4A8 variant, 128 x 256 tiles of 64 x 64 a wave): the activation tile
+// is the folded low plane and the e4m3 high plane of mq_quantize_act8, and each
+// product takes the low-plane MFMA and the high-plane one chained on its
+// result, 16 + 32 cycles of the matrix core, which bounds it (a 256 x 256 tile
+// of three times the bytes a row would leave LDS for one group in flight).
+// It replaced the streaming kernel's 64 x 64 tiles at large M, which fetch
+// every operand from L2 for each tile (4096 -> 14336 at M = 2048: 456 -> 185 us,
+// K = N = M = 4096: 262 -> 100 us).
+template <int WMB, int WAVES_N, bool RAW, bool SPLIT, bool A8 = false>
 __global__ __launch_bounds__(128 * WAVES_N, (WAVES_N == 2 ? 2 : 1))   // TileShape's kThreads, kPerCU
 void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ part) {
     using TS = TileShape<WMB, WAVES_N>;
@@ -295,17 +310,20 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     constexpr int WM = WMB, WN = 4;
     constexpr int kRow = kGroupBytes;                       // 64 bytes per row per group (W rows, X main plane)
     constexpr int kTile = kTB * kRow;                       // 8 KB: one 128-row tile
+    constexpr int kTailRow = A8 ? 128 : 32;                 // bytes of a row and group in the other plane
     constexpr int TM = TS::kTM, TN = TS::kTN, NBR = TS::kBlockRows, kWaves = TS::kWaves;
     constexpr int kCPerBR = WN / NBR;                       // a wave's sub-tiles per block row
     constexpr int kStages = 3;
     static_assert((NBR == 1 || NBR == 2) && kWaves == 4 * NBR, "one or two block rows, four waves per block row");
+    static_assert(!(A8 && SPLIT), "W4A8: no split-K");
     // X, W and weight scales: three slots, loaded two groups ahead; residual
     // tiles and their scales: two slots, loaded one group ahead (they are only
     // read after the dense pass).  Arrays by kind, so that a read of a slot
     // known at compile time is one lane address plus an immediate offset.
     struct Ring {
-        uint8_t x[kStages][TM * kRow];                      // activation main plane, 16-byte chunks swizzled
-        uint8_t xt[kStages][2][TM * 16];                    // activation tail plane: [quarter pair][row]
+        uint8_t x[kStages][TM * kRow];                      // activation main plane (A8: low plane), 16-byte chunks swizzled
+        uint8_t xt[kStages][TM * kTailRow];                 // activation tail plane: [quarter pair][row] (A8: high plane,
+                                                            // 16-byte chunk q of row r at chunk q ^ (r % 8))
         uint8_t w[kStages][TN * kRow];
         uint32_t sw[kStages][TN / 2];                       // fp16 scales, two per dword
         uint8_t r[2][NBR][kTile];
@@ -366,7 +384,9 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // m0.. is contiguous at (g M + m0) 64, its tails at (g M + m0) 32 of the
     // tail plane, that of block row br 8 KB at (g N + 128 br) 64, and R block
     // p is 8 KB.
-    const uint32_t tail0 = (uint32_t)G * (uint32_t)M * (uint32_t)kRow;
+    // A8: the high plane first, piece (g M + m0) 128, then the low plane (g M + m0) 64.
+    const uint32_t tail0 = A8 ? 0u : (uint32_t)G * (uint32_t)M * (uint32_t)kRow;
+    const uint32_t main0 = A8 ? (uint32_t)G * (uint32_t)M * 128u : 0u;
 
     // CSR walks of the tile's NBR block rows, from the first entry at or after
     // gb.  They read through the constant address space so they stay in scalar
@@ -408,16 +428,22 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // Lane l takes row 16 b + l / 4 and physical chunk l % 4, i.e. logical
     // chunk (l % 4) ^ swz(row) of that row, so each load instruction reads
     // 1 KB of whole 64-byte rows, contiguous.
-    static_assert(TM == 64 * WAVES_N && TN == 64 * WAVES_N && 8 * NBR == 4 * WAVES_N,
-                  "four X, W and R blocks per loader");
-    static_assert(TM / 32 == 2 * WAVES_N, "two tail-plane blocks per loader");
+    // (A8: low-plane blocks 2 ld, 2 ld + 1 and the high-plane blocks 4 ld .. + 3,
+    // eight rows of 128 bytes each: lane l takes row 8 b + l / 8 and physical
+    // chunk l % 8, logical chunk (l % 8) ^ (l / 8).)
+    constexpr int kXBlocks = A8 ? 2 : 4;                    // main-plane blocks per loader
+    static_assert(TM == 16 * kXBlocks * WAVES_N && TN == 64 * WAVES_N && 8 * NBR == 4 * WAVES_N,
+                  "kXBlocks X, four W and four R blocks per loader");
+    static_assert(TM * kTailRow == (A8 ? 4 : 2) * 1024 * WAVES_N, "two tail-plane or four high-plane blocks per loader");
     const bool loader = wm == 0;
     const int ld = wn, lbr = ld >> 1;
     // lane offsets of the first of the loader's four blocks (the swizzle of
     // row 16 b + l / 4 is (l / 8) % 4 for every b, so block k is 1024 k on)
-    const uint32_t vt = (uint32_t)(64 * ld + (lane >> 2)) * kRow + (((lane & 3) ^ ((lane >> 3) & 3)) << 4);
+    const uint32_t vt = (uint32_t)(16 * kXBlocks * ld + (lane >> 2)) * kRow + (((lane & 3) ^ ((lane >> 3) & 3)) << 4);
     const uint32_t vr = (uint32_t)(64 * (ld & 1) + (lane >> 2)) * kRow + (((lane & 3) ^ ((lane >> 3) & 3)) << 4);
     // tail blocks: quarter pair tq[k], rows trow[k] + l
+    // (A8: vhi, the lane offset of the first of the four high-plane blocks)
+    const uint32_t vhi = (uint32_t)(32 * ld + (lane >> 3)) * 128u + (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u;
     constexpr int kRowBlocks = TM / 64;                     // 64-row blocks of the tail tile per quarter pair
     int tq[2], trow[2];
     uint32_t vtl[2];
@@ -441,20 +467,27 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // 2^32), X is sent past its end, and a split's last two groups load those of
     // the next split.  X rows past M are other bytes of Xq (rows of the next
     // group, or of the tail plane): finite codes whose sums are not stored.
-    uint32_t xso = ((uint32_t)gb * (uint32_t)M + (uint32_t)m0) * kRow, xto = tail0 + xso / 2;
+    const uint32_t x0 = (uint32_t)gb * (uint32_t)M + (uint32_t)m0;
+    uint32_t xso = main0 + x0 * kRow, xto = tail0 + x0 * kTailRow;
     uint32_t wso = ((uint32_t)gb * (uint32_t)N + (uint32_t)(kTB * br[lbr])) * kRow;
     const bool has_s = !RAW && ld < NBR;
     uint32_t sso = ((uint32_t)gb * (uint32_t)N + (uint32_t)(kTB * br[ld < NBR ? ld : 0])) * 2u;
-    const uint32_t xend = (uint32_t)G * (uint32_t)M * kRow;                     // of the main plane
+    const uint32_t xend = (uint32_t)G * (uint32_t)M * (A8 ? 128u : (uint32_t)kRow);   // of the plane that comes first
     auto issue = [&](int slot) {
         if (!loader) return;
-        dma16x4(a.rx, lds_addr(&L.x[slot][(4 * ld) * 1024]), vt, xso < xend ? xso : kPastEnd);
+        if constexpr (A8) {
+            dma16x4(a.rx, lds_addr(&L.xt[slot][(4 * ld) * 1024]), vhi, xto < xend ? xto : kPastEnd);
+            dma16x2(a.rx, lds_addr(&L.x[slot][(2 * ld) * 1024]), vt, xso);
+        } else {
+            dma16x4(a.rx, lds_addr(&L.x[slot][(4 * ld) * 1024]), vt, xso < xend ? xso : kPastEnd);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) dma16s(a.rx, lds_addr(&L.xt[slot][tq[k]][trow[k] * 16]), vtl[k], xto);
+            for (int k = 0; k < 2; ++k)
+                dma16s(a.rx, lds_addr(&L.xt[slot][tq[k] * (TM * 16) + trow[k] * 16]), vtl[k], xto);
+        }
         dma16x4(a.rw, lds_addr(&L.w[slot][(4 * ld) * 1024]), vr, wso);            // rows of block row lbr
         if (has_s) dma4(a.rsw, lds_addr(&L.sw[slot][64 * ld]), (uint32_t)lane * 4, sso);
         xso += (uint32_t)M * kRow;
-        xto += (uint32_t)M * (kRow / 2);
+        xto += (uint32_t)M * kTailRow;
         wso += (uint32_t)N * kRow;
         sso += (uint32_t)N * 2u;
     };
@@ -517,13 +550,33 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     const uint32_t xo = lane_base(L.x, (uint32_t)(wrow + lrow) * kRow + swz_l);                   // + 1024 i
     const uint32_t to = lane_base(L.xt, (uint32_t)(lq >> 1) * (TM * 16) + (uint32_t)(wrow + lrow) * 16 +
                                             (uint32_t)(lq & 1) * 8);                           // + 256 i
+    // A8: the lane's 32 high-plane bytes are chunks 2 lq, 2 lq + 1 of the row
+    const uint32_t hswz = (uint32_t)((2 * lq) ^ (lrow & 7)) << 4;
+    const uint32_t ho0 = lane_base(L.xt, (uint32_t)(wrow + lrow) * 128u + hswz);               // + 2048 i
+    const uint32_t ho1 = lane_base(L.xt, (uint32_t)(wrow + lrow) * 128u + (hswz ^ 16u));
     const uint32_t wo = lane_base(L.w, (uint32_t)(16 * wn + lrow) * kRow + swz_l);      // + 1024 WAVES_N c
     const uint32_t so = lane_base(L.sw, (uint32_t)(16 * wn + lrow) * 2);                // + 32 WAVES_N c
     const uint32_t ro = lane_base(L.r, (uint32_t)(16 * wn + lrow) * kRow + swz_l);
     const uint32_t sro = lane_base(L.sr, (uint32_t)(16 * wn + lrow) * 2);
-    // the activation operand of sub-tile row i: main-plane chunk and tail
-    auto a_main = [&](int slot, int i) { return lds_read16(xo + TM * kRow * slot + 1024 * i); };
-    auto a_tail = [&](int slot, int i) { return lds_read8(to + TM * 32 * slot + 256 * i); };
+    // the activation operand of sub-tile row i, from main-plane chunk and tail
+    // (A8: the folded low-plane chunk, unfolded before its MFMAs, and the
+    // high-plane operand)
+    struct AOp {
+        i32x8 op;
+        uint4 lo;
+    };
+    auto a_read = [&](int slot, int i) {
+        AOp A;
+        if constexpr (A8) {
+            A.lo = lds_read16(xo + TM * kRow * slot + 1024 * i);
+            const uint4 h0 = lds_read16(ho0 + TM * kTailRow * slot + 2048 * i);
+            const uint4 h1 = lds_read16(ho1 + TM * kTailRow * slot + 2048 * i);
+            A.op = i32x8{(int)h0.x, (int)h0.y, (int)h0.z, (int)h0.w, (int)h1.x, (int)h1.y, (int)h1.z, (int)h1.w};
+        } else {
+            A.op = act_operand(lds_read16(xo + TM * kRow * slot + 1024 * i), lds_read8(to + TM * kTailRow * slot + 256 * i));
+        }
+        return A;
+    };
     // a weight or residual scale as an fp32 register value (kept out of the
     // fma, whose mixed-precision form measured slower)
     auto scale_f32 = [](uint16_t bits) {
@@ -537,8 +590,8 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // dense pass): the wave's four W fragments (folded), their scales and its
     // first A fragment.  The pass then starts without waiting for LDS.
     struct Ahead {
-        uint4 w[WN], a0;
-        uint2 a0t;
+        uint4 w[WN];
+        AOp a0;
         uint16_t s[WN];
     };
     auto read_ahead = [&](int slot, Ahead& H) {
@@ -547,8 +600,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             H.w[c] = lds_read16(wo + TN * kRow * slot + 1024 * WAVES_N * c);
             H.s[c] = RAW ? 0 : lds_read2(so + TN * 2 * slot + 32 * WAVES_N * c);
         }
-        H.a0 = a_main(slot, 0);
-        H.a0t = a_tail(slot, 0);
+        H.a0 = a_read(slot, 0);
     };
 
     // One pass over the staged group S.  The dense pass (RES == 0) multiplies
@@ -589,25 +641,31 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
         // before the epilogue of row i - 1, so each result is read several
         // MFMAs after it was started (no wait states to fill).
         f32x4 tq[2][WN];
-        auto a_row = [&](auto ic) -> i32x8 {
+        auto a_row = [&](auto ic) -> AOp {
             constexpr int i = decltype(ic)::value;
-            if constexpr (DENSE && i == 0) return act_operand(H.a0, H.a0t);
+            if constexpr (DENSE && i == 0) return H.a0;
             else {
-                const i32x8 av = act_operand(a_main(SL, i), a_tail(SL, i));
-                asm volatile("");       // keeps two rows' tail reads apart (merged, they need register moves)
-                return av;
+                const AOp A = a_read(SL, i);
+                if constexpr (!A8) asm volatile("");    // keeps two rows' tail reads apart (merged, they need register moves)
+                return A;
             }
         };
-        auto mfma_row = [&](auto ic, const i32x8 av) {
+        auto mfma_row = [&](auto ic, const i32x8 lo) {
             constexpr int i = decltype(ic)::value;
 #pragma unroll
             for (int c = 0; c < WN; ++c)
-                if (has(c)) tq[i & 1][c] = mfma_codes(av, b[c], f32x4{0.f, 0.f, 0.f, 0.f});
+                if (has(c)) tq[i & 1][c] = mfma_codes(lo, b[c], f32x4{0.f, 0.f, 0.f, 0.f});
         };
-        auto epilogue_row = [&](auto ic) {
+        auto mfma_row_hi = [&](auto ic, const AOp& A) {         // A8: + the high plane
             constexpr int i = decltype(ic)::value;
 #pragma unroll
-            for (int c = 0; c < WN; ++c) {
+            for (int c = 0; c < WN; ++c)
+                if (has(c)) tq[i & 1][c] = mfma_e4m3_codes(A.op, b[c], tq[i & 1][c]);
+        };
+        auto epilogue_cols = [&](auto ic, int c0, int c1) {
+            constexpr int i = decltype(ic)::value;
+#pragma unroll
+            for (int c = c0; c < c1; ++c) {
                 if (!has(c)) continue;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -617,6 +675,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
                 }
             }
         };
+        auto epilogue_row = [&](auto ic) { epilogue_cols(ic, 0, WN); };
         // Rows 0 .. WM - 1, software-pipelined.  The dense pass meets the
         // other waves after issuing the MFMAs of row kSync - 1 (its operand
         // for row kSync already read: the current slot is not touched by the
@@ -636,17 +695,36 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
         };
         // The activation operand is read two rows ahead (one row of MFMAs
         // and epilogue does not cover the LDS latency).
-        i32x8 av = a_row(std::integral_constant<int, 0>{});
-        i32x8 an = av;
+        AOp av = a_row(std::integral_constant<int, 0>{});
+        AOp an = av;
         if constexpr (WM > 1) an = a_row(std::integral_constant<int, 1>{});
         static_for<WM>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            i32x8 ann = an;
+            AOp ann = an;
             if constexpr (i + 2 < WM) ann = a_row(std::integral_constant<int, i + 2>{});
-            mfma_row(std::integral_constant<int, i>{}, av);
-            if constexpr (i > 0) {
-                epilogue_row(std::integral_constant<int, i - 1>{});
-                pin_row(i - 1);
+            if constexpr (A8) {
+                // low-plane MFMAs, half of the row before's epilogue, high-plane
+                // MFMAs, the other half (the scheduling barriers hold this order:
+                // left to itself the compiler put sums right behind the MFMAs
+                // they wait for: 4096 -> 14336 at M = 2048 189 -> 185 us)
+                const i32x8 lo = unfold_codes(av.lo);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_row(std::integral_constant<int, i>{}, lo);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (i > 0) epilogue_cols(std::integral_constant<int, i - 1>{}, 0, WN / 2);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_row_hi(std::integral_constant<int, i>{}, av);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (i > 0) {
+                    epilogue_cols(std::integral_constant<int, i - 1>{}, WN / 2, WN);
+                    pin_row(i - 1);
+                }
+            } else {
+                mfma_row(std::integral_constant<int, i>{}, av.op);
+                if constexpr (i > 0) {
+                    epilogue_row(std::integral_constant<int, i - 1>{});
+                    pin_row(i - 1);
+                }
             }
             if constexpr (DENSE && i == kSync - 1) {
                 wait_loads_and_sync();      // the only loads in flight are those issued one group ago
@@ -1718,10 +1796,23 @@ extern "C" mq_status mq_fused_gemm_acc_i32(mq_variant variant, int M, int N, int
 }
 
 // ---------------------------------------------------------------------------
-// W4A8 (per-token INT8 activations): the streaming kernels for every M --
-// decode tiles up to 32 rows, 64 x 64 tiles (32 x 64 when those are fewer
-// than the CUs) above.
+// W4A8 (per-token INT8 activations): decode tiles of the streaming kernel up to
+// 32 rows; above, the tiled kernel where its tiles are enough, else 64 x 64
+// streaming tiles (32 x 64 when those are fewer than the CUs).
 // ---------------------------------------------------------------------------
+// The tiled kernel takes a W4A8 layer when its 128 x 256 tiles need at most a
+// third of the rounds of the 64 x 64 streaming tiles (one workgroup a CU in
+// both): a tiled round measured 2.7 to 2.9 streaming ones (K = 4096: 47 against
+// 16 to 17 us; K = 14336: 143 against 47 to 50).  Three rounds against one:
+// 5120 -> 5120 at M = 512 57.0 us tiled, 61.6 streamed; four: 4096 -> 4096 at
+// M = 1024 47.6 and 68.0, 8192 -> 28672 at M = 128 92 and 116; two: 4096 -> 4096
+// at M = 512 47 and 37, 8192 -> 28672 at M = 64 91 and 63.
+static bool a8_tiled_preferred(int M, int N) {
+    if (N % TileShape<4, 4>::kTN != 0) return false;
+    const int64_t tt = (int64_t)((M + 127) / 128) * (N / 256), ts = (int64_t)((M + 63) / 64) * (N / 64);
+    return (ts + kCUs - 1) / kCUs >= 3 * ((tt + kCUs - 1) / kCUs);
+}
+
 template <bool RAW>
 static mq_status launch_a8(GemmArgs a, hipStream_t stream) {
     const mq_status rs = operand_resources<RAW>(a, true);
@@ -1734,6 +1825,16 @@ static mq_status launch_a8(GemmArgs a, hipStream_t stream) {
         if (decode_spw(a.N) >= 2) launch_stream<2, 2, 1, 1, RAW, false, true>(a, 0, stream);
         else launch_stream<2, 1, 1, 1, RAW, false, true>(a, 0, stream);
     } else {
+        using TS = TileShape<4, 4>;
+        const int64_t tiles = (int64_t)((a.M + TS::kTM - 1) / TS::kTM) * (a.N / TS::kTN);
+        if (a8_tiled_preferred(a.M, a.N)) {
+            if (tiles > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
+            a.y16 = (!RAW && a.Y && mq_host::aligned(a.Y, 16)) ? 1 : 0;
+            a.rank_rows = tiles <= kCUs;
+            hipLaunchKernelGGL((gemm_tiled_kernel<4, 4, RAW, false, true>), dim3((unsigned)tiles), dim3(TS::kThreads), 0,
+                               stream, a, 0, (float*)nullptr);
+            return mq_host::launch_status();
+        }
         const int64_t t64 = (int64_t)((a.M + 63) / 64) * (a.N / 64);
         const int64_t t32 = (int64_t)((a.M + 31) / 32) * (a.N / 64);
         if (t32 > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
