@@ -58,6 +58,7 @@ struct GemmArgs {
     const uint16_t* X;       // fused-quantisation decode path: fp16 activations
     int ldx;
     int nnzb;
+    int tile_rows;           // tiled kernels with PART: rows of a tile (a multiple of 32, at most the tile's height)
     int rank_rows;           // tiled kernels: order block rows by residual count (one-round grids)
     int y16;                 // Y 16-byte aligned: the tiled kernels store Y in 16-byte row pieces
     // byte sizes of Xq, Wq, Rq, s_w, s_r (each below 2 GB) and buffer
@@ -169,6 +170,21 @@ __device__ __forceinline__ void tile_coords(int b, int tiles_m, int tiles_n, int
     const int r = t - band * kGroupM * tiles_n;
     tm = first + r % h;
     tn = r / h;
+}
+// The same for a grid whose last tile row is shorter: every XCD takes its
+// share of the full tiles first and its share of the short ones last, where
+// they fill the round that the full tiles leave unfinished.
+__device__ __forceinline__ void tile_coords_short_last(int b, int tiles_m, int tiles_n, int& tm, int& tn) {
+    const int full = (tiles_m - 1) * tiles_n, xcd = b % 8, k = b / 8;
+    const int mine = full / 8 + (xcd < full % 8);                // full tiles of this XCD
+    if (k < mine) {
+        tile_coords(b, tiles_m - 1, tiles_n, tm, tn);
+        return;
+    }
+    // the short tiles of the XCDs before this one: all their tiles less the full ones
+    auto before = [&](int n) { return xcd * (n / 8) + min(xcd, n % 8); };
+    tm = tiles_m - 1;
+    tn = before(full + tiles_n) - before(full) + k - mine;
 }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
@@ -302,7 +318,12 @@ struct TileShape {
 // It replaced the streaming kernel's 64 x 64 tiles at large M, which fetch
 // every operand from L2 for each tile (4096 -> 14336 at M = 2048: 456 -> 185 us,
 // K = N = M = 4096: 262 -> 100 us).
-template <int WMB, int WAVES_N, bool RAW, bool SPLIT, bool A8 = false>
+// PART: tiles of a.tile_rows rows (256, 192 or 128) and a last tile row that is
+// as high as its rows of Y need, in steps of 64 rows; sub-tile rows past it are
+// not multiplied.  Work on rows that are not there was up to half of a launch:
+// 4096 -> 14336 at M = 1157 ran two rounds of 256-row tiles, the second with 24
+// of 280 tiles, and a fifth of all tiles had 133 rows (84.5 -> 72 us).
+template <int WMB, int WAVES_N, bool RAW, bool SPLIT, bool A8 = false, bool PART = false>
 __global__ __launch_bounds__(128 * WAVES_N, (WAVES_N == 2 ? 2 : 1))   // TileShape's kThreads, kPerCU
 void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ part) {
     using TS = TileShape<WMB, WAVES_N>;
@@ -340,10 +361,12 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int lrow = lane & 15, lq = lane >> 4;
-    const int tiles_m = (M + TM - 1) / TM, tiles_n = N / TN;
+    const int th = PART ? a.tile_rows : TM;                 // rows of a tile
+    const int tiles_m = (M + th - 1) / th, tiles_n = N / TN;
     int tm, tn;
-    tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    const int m0 = tm * TM;
+    if (PART && M % th != 0) tile_coords_short_last(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    else tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    const int m0 = tm * th;
     const int gb = SPLIT ? blockIdx.y * groups_per_split : 0;
     const int ge = SPLIT ? min(G, gb + groups_per_split) : G;
 
@@ -532,7 +555,10 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // c = 0 .. 3 at tile columns 16 (wn + WAVES_N c) .., interleaved so that
     // every wave has kCPerBR sub-tiles in each residual block row: a residual
     // block keeps all the waves busy, not only those of its block row.
-    const int wrow = 16 * WM * wm;
+    // (PART: half the tile's rows each, nrow sub-tile rows of them; a last tile
+    // is as high as its rows of Y need)
+    const int nrow = PART ? min(th, (M - m0 + 31) & ~31) / 32 : WM;
+    const int wrow = 16 * nrow * wm;
 
     // LDS reads.  Every row and column this lane reads has the same swizzle
     // (rows wrow + 16 i + lrow, columns 16 (wn + WAVES_N c) + lrow: (row / 2) % 4
@@ -614,8 +640,9 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // the R fragments of that block row from residual slot RS.  The fp32 path
     // accumulates scale x (group sum / 64); the factor 64 is applied once, in
     // the final epilogue (exact).
-    constexpr int kSync = WM / 2;
-    auto phase = [&](auto slot_c, auto res_c, Ahead& H, int rs, const int (&rp_next)[NBR]) {
+    auto phase = [&](auto slot_c, auto res_c, auto rows_c, Ahead& H, int rs, const int (&rp_next)[NBR]) {
+        constexpr int NR = decltype(rows_c)::value;             // sub-tile rows 0 .. NR - 1
+        constexpr int kSync = NR / 2;
         constexpr int SL = decltype(slot_c)::value, SNEXT = SL == kStages - 1 ? 0 : SL + 1;
         constexpr int RES = decltype(res_c)::value;
         constexpr bool DENSE = RES == 0;
@@ -697,11 +724,11 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
         // and epilogue does not cover the LDS latency).
         AOp av = a_row(std::integral_constant<int, 0>{});
         AOp an = av;
-        if constexpr (WM > 1) an = a_row(std::integral_constant<int, 1>{});
-        static_for<WM>([&](auto ic) {
+        if constexpr (NR > 1) an = a_row(std::integral_constant<int, 1>{});
+        static_for<NR>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             AOp ann = an;
-            if constexpr (i + 2 < WM) ann = a_row(std::integral_constant<int, i + 2>{});
+            if constexpr (i + 2 < NR) ann = a_row(std::integral_constant<int, i + 2>{});
             if constexpr (A8) {
                 // low-plane MFMAs, half of the row before's epilogue, high-plane
                 // MFMAs, the other half (the scheduling barriers hold this order:
@@ -735,8 +762,8 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             av = an;
             an = ann;
         });
-        epilogue_row(std::integral_constant<int, WM - 1>{});
-        pin_row(WM - 1);
+        epilogue_row(std::integral_constant<int, NR - 1>{});
+        pin_row(NR - 1);
     };
 
     // residual blocks of the current group and of the groups one and two
@@ -764,23 +791,36 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // multiplies its kCPerBR sub-tiles of that block row.  (Passes rather than
     // variants of the dense code: one code path per group keeps the
     // accumulators in fixed registers.)
-    auto step = [&](auto slot_c, int g) {
+    auto step = [&](auto slot_c, auto rows_c, int g) {
         next_blocks(g + 2, p_new);
         const int rs = g & 1;
-        phase(slot_c, std::integral_constant<int, 0>{}, H, rs, p_next);
-        if (p_cur[0] >= 0) phase(slot_c, std::integral_constant<int, kBR0>{}, H, rs, p_next);
+        phase(slot_c, std::integral_constant<int, 0>{}, rows_c, H, rs, p_next);
+        if (p_cur[0] >= 0) phase(slot_c, std::integral_constant<int, kBR0>{}, rows_c, H, rs, p_next);
         if constexpr (NBR == 2)
-            if (p_cur[1] >= 0) phase(slot_c, std::integral_constant<int, kBR0 << kCPerBR>{}, H, rs, p_next);
+            if (p_cur[1] >= 0) phase(slot_c, std::integral_constant<int, kBR0 << kCPerBR>{}, rows_c, H, rs, p_next);
 #pragma unroll
         for (int b = 0; b < NBR; ++b) {
             p_cur[b] = p_next[b];
             p_next[b] = p_new[b];
         }
     };
-    for (int g = gb; g < ge; g += kStages) {
-        step(std::integral_constant<int, 0>{}, g);
-        if (g + 1 < ge) step(std::integral_constant<int, 1>{}, g + 1);
-        if (g + 2 < ge) step(std::integral_constant<int, 2>{}, g + 2);
+    auto run = [&](auto rows_c) {
+        for (int g = gb; g < ge; g += kStages) {
+            step(std::integral_constant<int, 0>{}, rows_c, g);
+            if (g + 1 < ge) step(std::integral_constant<int, 1>{}, rows_c, g + 1);
+            if (g + 2 < ge) step(std::integral_constant<int, 2>{}, rows_c, g + 2);
+        }
+    };
+    if constexpr (PART) {
+        // code of its own for each height, chosen once (a branch around every
+        // row inside one loop made the compiler copy the sums: five times slower)
+        static_assert(WM == 8, "heights of the 256-row tile");
+        if (nrow > 6) run(std::integral_constant<int, 8>{});
+        else if (nrow > 4) run(std::integral_constant<int, 6>{});
+        else if (nrow > 2) run(std::integral_constant<int, 4>{});
+        else run(std::integral_constant<int, 2>{});
+    } else {
+        run(std::integral_constant<int, WM>{});
     }
     // the X and W loads issued for the two groups past the end read nothing,
     // but they still write a ring slot: let them finish first
@@ -805,6 +845,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             __syncthreads();                              // every wave is done with the ring
 #pragma unroll
             for (int i = 0; i < WM; ++i) {
+                if (PART && i >= nrow) continue;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int rl = wrow + 16 * i + 4 * lq + r;
@@ -818,7 +859,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             }
             __syncthreads();
             constexpr int kPiecesPerRow = TN / 8;
-            const int rows = min(TM, M - m0);
+            const int rows = min(th, M - m0);
             for (int q = t; q < rows * kPiecesPerRow; q += TS::kThreads) {
                 const int rl = q / kPiecesPerRow, lc = 8 * (q % kPiecesPerRow);
                 const int n = kTB * br[lc / kTB] + (lc & (kTB - 1));
@@ -830,6 +871,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     }
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
+        if (PART && i >= nrow) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = m0 + wrow + 16 * i + 4 * lq + r;
@@ -1569,13 +1611,48 @@ static void launch_decode(const GemmArgs& a, int spw, size_t xs_bytes, hipStream
 // 5120 -> 25600 at M = 768, 117 against 127 us, 4096 -> 14336 at M = 1536,
 // 102.5 against 107.6, 14336 -> 4096 at M = 6144 and 5120 -> 5120 at
 // M = 4096, and slower only on K = N = 4096 at M = 5120, 100.5 against 94.7.)
-constexpr int kLargeRoundPct = 100, kSmallRoundPct = 68;
+constexpr int kSmallRoundPct = 68;
+
+// Time of a tile of the large kernel with this many rows, in per cent of a
+// 256-row one (K = 4096: rounds of 42.6, 38.7 and 30.0 us with 256, 192 and 128
+// rows; below 128 the group's latencies are what is left).
+static int tile_height_pct(int rows) {
+    return rows > 192 ? 100 : rows > 128 ? 88 : 70;
+}
+
+// Estimated time of the large kernel on tiles of th rows, in the same units:
+// whole rounds of full tiles, then the last round, in which the CUs without a
+// full tile take the short tiles of the last tile row in turn.
+static int64_t large_time_pct(int M, int N, int th) {
+    const int64_t tn = N / 256, full = (M / th) * tn, last = M % th ? tn : 0, rem = full % kCUs;
+    const int c = tile_height_pct(th), ct = tile_height_pct(M % th);
+    int64_t left = last, t = 0;
+    while (left > 0 && (rem == 0 || t < c)) {
+        left -= kCUs - rem;
+        t += ct;
+    }
+    while (left > 0) {
+        left -= kCUs;
+        t = (t > c ? t : c) + ct;
+    }
+    return full / kCUs * c + (rem > 0 && t < c ? c : t);
+}
+
+// Rows of the large kernel's tiles: 256, or 192 or 128 where lower tiles fill
+// the rounds better (5120 -> 5120 at M = 2048: 160 tiles of 256 rows leave 96 CUs
+// idle, 220 of 192 rows run in one round as well, 56.6 -> 48.5 us; 4096 -> 14336 at
+// M = 1280: 280 tiles are two rounds, 85.2 -> 77.8 us).
+static int large_tile_rows(int M, int N) {
+    int best = 256;
+    for (int th = 192; th >= 128; th -= 64)
+        if (large_time_pct(M, N, th) < large_time_pct(M, N, best)) best = th;
+    return best;
+}
+
 static bool large_tiles_fit(int M, int N) {
     if (N % 256 != 0) return false;
-    const int64_t tl = (int64_t)((M + 255) / 256) * (N / 256);
-    const int64_t ts = (int64_t)((M + 127) / 128) * (N / 128);
-    const int64_t rl = (tl + kCUs - 1) / kCUs, rs = (ts + 2 * kCUs - 1) / (2 * kCUs);
-    return kLargeRoundPct * rl < kSmallRoundPct * rs;
+    const int64_t ts = (int64_t)((M + 127) / 128) * (N / 128), rs = (ts + 2 * kCUs - 1) / (2 * kCUs);
+    return large_time_pct(M, N, large_tile_rows(M, N)) < kSmallRoundPct * rs;
 }
 
 // Buffer resource words, built on the host: base[31:0]; base[47:32] (stride
@@ -1663,11 +1740,16 @@ static mq_status launch(mq_variant variant, const GemmArgs& args, void* workspac
         launch_medium_tiles<RAW>(a, t64 >= kCUs, stream);
     } else if (variant == MQ_VARIANT_TILED_LARGE) {
         using TS = TileShape<8, 4>;
-        const int64_t tiles = (int64_t)((a.M + TS::kTM - 1) / TS::kTM) * (a.N / TS::kTN);
+        a.tile_rows = large_tile_rows(a.M, a.N);
+        const int64_t tiles = (int64_t)((a.M + a.tile_rows - 1) / a.tile_rows) * (a.N / TS::kTN);
         if (tiles > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
         a.rank_rows = tiles <= (int64_t)kCUs * TS::kPerCU;
-        hipLaunchKernelGGL((gemm_tiled_kernel<8, 4, RAW, false>), dim3((unsigned)tiles), dim3(TS::kThreads), 0,
-                           stream, a, 0, (float*)nullptr);
+        if (a.tile_rows == TS::kTM && a.M % TS::kTM == 0)
+            hipLaunchKernelGGL((gemm_tiled_kernel<8, 4, RAW, false>), dim3((unsigned)tiles), dim3(TS::kThreads), 0,
+                               stream, a, 0, (float*)nullptr);
+        else
+            hipLaunchKernelGGL((gemm_tiled_kernel<8, 4, RAW, false, false, true>), dim3((unsigned)tiles),
+                               dim3(TS::kThreads), 0, stream, a, 0, (float*)nullptr);
     } else if (variant == MQ_VARIANT_SKINNY) {
         if (a.M <= 16) launch_decode<1, RAW, false>(a, a.M == 1 ? decode_spw_one_row(a.N) : decode_spw(a.N), 0, stream);
         else launch_decode<2, RAW, false>(a, decode_spw(a.N), 0, stream);
