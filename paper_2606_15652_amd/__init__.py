@@ -86,15 +86,25 @@ def load(path: str = LIB_PATH) -> C.CDLL:
 
 
 # ------------------------------------------------------------------ utils --
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
-def _stream(stream=None):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+def _stream(stream=None) -> int:
+    """The hipStream_t of `stream`, or of the current device's current stream
+    (read as a number: building torch's Stream object for it takes 3 us, a
+    quarter of the host time of a one-token layer call: linear 11.3 -> 8.7 us)."""
+    if stream is not None:
+        return stream.cuda_stream
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _ptr(t) -> Optional[int]:
