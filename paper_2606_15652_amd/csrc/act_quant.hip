@@ -1,25 +1,26 @@
-// Per-token symmetric INT4 activation quantisation fused with code packing
+// Per-token symmetric activation quantisation fused with code packing
 // (Section 2, Eq. (1) applied per row; Section 4.2 "Kernel Fusion": layout
-// packing is fused with quantisation).
+// packing is fused with quantisation): INT4 codes in the matrix instruction's
+// operand form, or (W4A8) INT8 codes as an e4m3 high plane and a folded 4-bit
+// low plane.
 //
-// One workgroup of 256 threads per token row.  Each thread owns 32-byte
-// chunks (16 fp16) of the row; the row maximum of |x| is taken on the fp16 bit
-// patterns with the sign cleared (an order-preserving integer max for finite
-// values, packed 16-bit maxima), reduced across the wave with xor-shuffles and
-// across the four waves through LDS.  Codes are then formed from the
-// registers (rows up to CPT * 4096 elements) or by re-reading the row (longer
-// rows), with the division-free exact rounding of quant_mag, and written in
-// the matrix instruction's operand form (act_main_offset / act_tail_offset):
-// the 16 codes of an even chunk are dwords d0 .. d2 of their quarter, those of
-// the odd chunk d3 .. d5.  The pair of threads of a quarter exchange d3, so
-// that the even thread writes the quarter's 16 main-plane bytes and the odd
-// one its 8 tail bytes (the quarters of a group are then 64 and 32 contiguous
-// bytes).
+// One workgroup per token row, one thread per quarter of a group (32 codes,
+// 64 bytes of X), up to 1024 threads: a row of up to 32768 values is read once,
+// in one trip to memory, and stays in registers.  The row maximum of |x| is
+// taken on the fp16 bit patterns with the sign cleared (an order-preserving
+// integer max for finite values, packed 16-bit maxima), reduced across the wave
+// by DPP and across the waves through LDS.  Large inputs are bound by memory
+// and, close behind, by the VALU work per code: a code is five fp32 operations
+// and a clamp, and one conversion instruction turns the thread's 32 codes into
+// their six operand dwords.  Few rows are bound by latency.  (256 threads of up
+// to 16 chunks of 16 codes, packed with integer operations, against this: INT4
+// 4096 x 4096 11.0 -> 9.4 us, 8192 x 8192 33.0 -> 27.3; INT8 2048 x 4096
+// 11.2 -> 7.4, 16 x 14336 11.0 -> 4.1.)
 #include "mq_device.h"
 
 namespace mq {
 
-constexpr int kActThreads = 256;
+constexpr int kActMaxThreads = 1024;
 
 // Row of workgroup b.  Workgroups go to the eight XCDs in turn (b % 8), and
 // neighbouring rows share the 128-byte lines of the operand planes (a row
@@ -31,197 +32,135 @@ __device__ __forceinline__ int xcd_row(int b, int M) {
     return x * per + min(x, rem) + k;
 }
 
-// CPT > 0: the row stays in registers (CPT chunks per thread); CPT == 0: the
-// row is read twice.
-template <int CPT>
-__global__ __launch_bounds__(kActThreads) void act_quant_kernel(
+struct Quarter {
+    uint4 v[4];                                            // 32 fp16
+};
+__device__ __forceinline__ Quarter load_quarter(const uint16_t* p) {
+    Quarter q;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q.v[i] = reinterpret_cast<const uint4*>(p)[i];
+    return q;
+}
+__device__ __forceinline__ uint32_t quarter_absmax_bits(const Quarter& q) {
+    const uint32_t a = chunk_absmax_bits(q.v[0], q.v[1]), b = chunk_absmax_bits(q.v[2], q.v[3]);
+    return a > b ? a : b;
+}
+
+// Largest v of the wave (v >= 0), by DPP: row shifts, then the row broadcasts
+// that carry a row's maximum on; lane 63 has the result.
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
+    auto step = [&](auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
+        v = o > v ? o : v;
+    };
+    step(std::integral_constant<int, 0x111>{});             // row_shr:1, 2, 4, 8
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});             // row_bcast:15
+    step(std::integral_constant<int, 0x143>{});             // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The 32 codes of a quarter as fp32 integers (+0 for zero): quant_mag's steps on
+// the signed value, which hold for qmax = 127 as well: a quotient that is not a
+// tie is at least 2^-13 from one, q1 within 2^-17 of it (2^-24 relative).
+__device__ __forceinline__ void quarter_codes(const Quarter& x, float s, float inv_s, float qmax, float (&q)[32]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t w[4] = {x.v[i].x, x.v[i].y, x.v[i].z, x.v[i].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float f = half_bits_to_float((uint16_t)(e & 1 ? w[e >> 1] >> 16 : w[e >> 1] & 0xFFFFu));
+            const float q0 = f * inv_s;
+            const float q1 = __builtin_fmaf(__builtin_fmaf(-q0, s, f), inv_s, q0);
+            q[8 * i + e] = __builtin_amdgcn_fmed3f(rintf(q1) + 0.0f, -qmax, qmax);
+        }
+    }
+}
+
+// 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
+// bit 6e; the instruction takes the even codes and the odd ones).
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+__device__ __forceinline__ u32x6 operand_dwords(const float (&q)[32]) {
+    f32x16 even, odd;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        even[i] = q[2 * i];
+        odd[i] = q[2 * i + 1];
+    }
+    return __builtin_bit_cast(u32x6, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, 8.0f));
+}
+
+// LOOP: rows longer than 32 codes a thread, read a second time for the codes.
+template <bool A8, bool LOOP>
+__global__ __launch_bounds__(kActMaxThreads) void act_quant_kernel(
     const uint16_t* __restrict__ X, int M, int K, int ldx,
     uint8_t* __restrict__ Xq, uint16_t* __restrict__ s_x) {
-    __shared__ uint32_t red[kActThreads / 64];
+    __shared__ uint32_t red[kActMaxThreads / 64];
     const int m = xcd_row(blockIdx.x, M);
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, threads = blockDim.x;
     const uint16_t* row = X + (int64_t)m * ldx;
-    const int nchunks = K / 16, G = K / 128;
-    // chunk c (codes 16c .. 16c+15) is half c % 2 of quarter (c / 2) % 4 of group c / 8
-    // (both threads of a pair are active or neither: K / 16 is even)
-    auto store = [&](int c, const uint4 v0, const uint4 v1, float s, float inv_s) {
-        uint32_t o0, o1, o2;
-        quant_fields(v0, v1, s, inv_s, o0, o1, o2);
-        const uint32_t d3 = __shfl_down(o0, 1, 64);          // the odd neighbour's o0
-        const int g = c >> 3, j = (c >> 1) & 3;
-        if ((c & 1) == 0)
-            *reinterpret_cast<uint4*>(Xq + act_main_offset(M, m, g) + 16 * j) = make_uint4(o0, o1, o2, d3);
-        else
-            *reinterpret_cast<uint2*>(Xq + act_tail_offset(M, G, m, g, j)) = make_uint2(o1, o2);
-    };
+    const int nq = K / 32, G = K / kGroup;
 
+    Quarter v = {};
     uint32_t amax = 0;
-    uint4 v[CPT > 0 ? CPT : 1][2];
-    if constexpr (CPT > 0) {
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int c = t + i * kActThreads;
-            if (c < nchunks) {
-                v[i][0] = *reinterpret_cast<const uint4*>(row + 16 * c);
-                v[i][1] = *reinterpret_cast<const uint4*>(row + 16 * c + 8);
-                const uint32_t cm = chunk_absmax_bits(v[i][0], v[i][1]);
-                amax = cm > amax ? cm : amax;
-            }
-        }
-    } else {
-        for (int c = t; c < nchunks; c += kActThreads) {
-            const uint32_t cm = chunk_absmax_bits(*reinterpret_cast<const uint4*>(row + 16 * c),
-                                                  *reinterpret_cast<const uint4*>(row + 16 * c + 8));
-            amax = cm > amax ? cm : amax;
-        }
+    for (int c = t; c < nq; c += threads) {
+        v = load_quarter(row + 32 * c);
+        const uint32_t cm = quarter_absmax_bits(v);
+        amax = cm > amax ? cm : amax;
+        if constexpr (!LOOP) break;
     }
-    amax = wave_max_u32(amax);
+    amax = wave_max_dpp(amax);
     if ((t & 63) == 0) red[t >> 6] = amax;
     __syncthreads();
-    amax = red[0];
-#pragma unroll
-    for (int w = 1; w < kActThreads / 64; ++w) amax = red[w] > amax ? red[w] : amax;
+    for (int w = 0; w < threads / 64; ++w) amax = red[w] > amax ? red[w] : amax;
 
-    const uint16_t sb = scale_bits_from_amax(half_bits_to_float((uint16_t)amax));
+    constexpr int qmax = A8 ? kQmax8 : kQmax;
+    const uint16_t sb = scale_bits_from_amax(half_bits_to_float((uint16_t)amax), qmax);
     const float s = half_bits_to_float(sb);
-    const float inv_s = 1.0f / s;
+    const float inv_s = s == 0.0f ? 0.0f : 1.0f / s;        // a zero scale: all codes 0
     if (t == 0) s_x[m] = sb;
 
-    if constexpr (CPT > 0) {
+    for (int c = t; c < nq; c += threads) {
+        if constexpr (LOOP) v = load_quarter(row + 32 * c);
+        float q[32];
+        quarter_codes(v, s, inv_s, (float)qmax, q);
+        const int g = c >> 2, j = c & 3;                    // quarter j of group g
+        if constexpr (A8) {
+            // x = 8 h + l: the e4m3 bytes of h = floor(x / 8) in the high plane (piece (row, group)
+            // of 128 bytes at (g M + m) 128, chunks placed by hi_chunk_offset), the folded 4-bit
+            // codes l in [0, 7] in the low plane (M K bytes on, the W4A4 group order)
+            uint32_t hb[8];
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int c = t + i * kActThreads;
-            if (c < nchunks) store(c, v[i][0], v[i][1], s, inv_s);
-        }
-    } else {
-        for (int c = t; c < nchunks; c += kActThreads)
-            store(c, *reinterpret_cast<const uint4*>(row + 16 * c), *reinterpret_cast<const uint4*>(row + 16 * c + 8),
-                  s, inv_s);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// W4A8: per-token symmetric INT8 codes (Eq. (1) with q_max = 127; the W4A8
-// setting of the appendix "Implementation Details", per-token dynamic
-// activation quantisation), written as x = 8 h + l: the e4m3 bytes of h in
-// the high plane (piece (row, group) of 128 bytes at (g M + m) 128, chunks
-// placed by hi_chunk_offset) and the
-// folded 4-bit codes l in [0, 7] in the low plane (M K bytes on, the W4A4
-// group order).  Same row structure as act_quant_kernel.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void quant8_chunk(const uint4 v0, const uint4 v1, float s, float inv_s,
-                                             uint4& hi, uint2& lo) {
-    const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-    int l[16];
-    uint32_t hb[4] = {0u, 0u, 0u, 0u};
+            for (int i = 0; i < 8; ++i) {
+                float h[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const float x = half_bits_to_float((uint16_t)(e & 1 ? w[e >> 1] >> 16 : w[e >> 1] & 0xFFFFu));
-        const int q = s == 0.0f ? 0 : quant_code_max(x, s, inv_s, kQmax8);
-        const int h = q >> 3;                                    // floor(q / 8)
-        l[e] = q - 8 * h;
-        hb[e >> 2] |= e4m3_of_int(h) << (8 * (e & 3));
-    }
-    hi = make_uint4(hb[0], hb[1], hb[2], hb[3]);
-    lo = fold_codes(l);
-}
-
-template <int CPT>
-__global__ __launch_bounds__(kActThreads) void act_quant8_kernel(
-    const uint16_t* __restrict__ X, int M, int K, int ldx,
-    uint8_t* __restrict__ Xq8, uint16_t* __restrict__ s_x) {
-    __shared__ uint32_t red[kActThreads / 64];
-    const int m = xcd_row(blockIdx.x, M);
-    const int t = threadIdx.x;
-    const uint16_t* row = X + (int64_t)m * ldx;
-    const int nchunks = K / 16;
-    uint8_t* lo_plane = Xq8 + (int64_t)M * K;
-    auto store = [&](int c, const uint4 v0, const uint4 v1, float s, float inv_s) {
-        uint4 hi;
-        uint2 lo;
-        quant8_chunk(v0, v1, s, inv_s, hi, lo);
-        const int g = c >> 3, cc = c & 7;
-        *reinterpret_cast<uint4*>(Xq8 + ((int64_t)g * M + m) * 128 + hi_chunk_offset(cc)) = hi;
-        *reinterpret_cast<uint2*>(lo_plane + piece_offset(M, m, g) + 8 * cc) = lo;
-    };
-
-    uint32_t amax = 0;
-    uint4 v[CPT > 0 ? CPT : 1][2];
-    if constexpr (CPT > 0) {
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int c = t + i * kActThreads;
-            if (c < nchunks) {
-                v[i][0] = *reinterpret_cast<const uint4*>(row + 16 * c);
-                v[i][1] = *reinterpret_cast<const uint4*>(row + 16 * c + 8);
-                const uint32_t cm = chunk_absmax_bits(v[i][0], v[i][1]);
-                amax = cm > amax ? cm : amax;
+                for (int e = 0; e < 4; ++e) {
+                    h[e] = floorf(q[4 * i + e] * 0.125f);
+                    q[4 * i + e] = __builtin_fmaf(-8.0f, h[e], q[4 * i + e]);
+                }
+                int b = __builtin_amdgcn_cvt_pk_fp8_f32(h[0], h[1], 0, false);
+                hb[i] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(h[2], h[3], b, true);
             }
+            const u32x6 d = operand_dwords(q);
+            uint8_t* hi = Xq + ((int64_t)g * M + m) * 128;
+            *reinterpret_cast<uint4*>(hi + hi_chunk_offset(2 * j)) = make_uint4(hb[0], hb[1], hb[2], hb[3]);
+            *reinterpret_cast<uint4*>(hi + hi_chunk_offset(2 * j + 1)) = make_uint4(hb[4], hb[5], hb[6], hb[7]);
+            *reinterpret_cast<uint4*>(Xq + (int64_t)M * K + piece_offset(M, m, g) + 16 * j) =
+                make_uint4(d[0] | (d[2] & kFoldA), d[1] | (d[2] & kFoldB), d[3] | (d[5] & kFoldA), d[4] | (d[5] & kFoldB));
+        } else {
+            const u32x6 d = operand_dwords(q);
+            *reinterpret_cast<uint4*>(Xq + act_main_offset(M, m, g) + 16 * j) = make_uint4(d[0], d[1], d[2], d[3]);
+            *reinterpret_cast<uint2*>(Xq + act_tail_offset(M, G, m, g, j)) = make_uint2(d[4], d[5]);
         }
-    } else {
-        for (int c = t; c < nchunks; c += kActThreads) {
-            const uint32_t cm = chunk_absmax_bits(*reinterpret_cast<const uint4*>(row + 16 * c),
-                                                  *reinterpret_cast<const uint4*>(row + 16 * c + 8));
-            amax = cm > amax ? cm : amax;
-        }
-    }
-    amax = wave_max_u32(amax);
-    if ((t & 63) == 0) red[t >> 6] = amax;
-    __syncthreads();
-    amax = red[0];
-#pragma unroll
-    for (int w = 1; w < kActThreads / 64; ++w) amax = red[w] > amax ? red[w] : amax;
-
-    const uint16_t sb = scale_bits_from_amax(half_bits_to_float((uint16_t)amax), kQmax8);
-    const float s = half_bits_to_float(sb);
-    const float inv_s = 1.0f / s;
-    if (t == 0) s_x[m] = sb;
-
-    if constexpr (CPT > 0) {
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int c = t + i * kActThreads;
-            if (c < nchunks) store(c, v[i][0], v[i][1], s, inv_s);
-        }
-    } else {
-        for (int c = t; c < nchunks; c += kActThreads)
-            store(c, *reinterpret_cast<const uint4*>(row + 16 * c), *reinterpret_cast<const uint4*>(row + 16 * c + 8),
-                  s, inv_s);
+        if constexpr (!LOOP) break;
     }
 }
 
-}  // namespace mq
-
-using namespace mq;
-
-extern "C" mq_status mq_quantize_act8(const void* X, int M, int K, int ldx,
-                                      uint8_t* Xq8, void* s_x, hipStream_t stream) {
-    if (M < 0 || K < 0) return MQ_ERR_INVALID_ARG;
-    if (M > (1 << 24) || K < 128 || K % 128 != 0 || K > (1 << 20) || ldx < K || ldx % 8 != 0)
-        return MQ_ERR_UNSUPPORTED_SHAPE;
-    if (M == 0) return MQ_OK;
-    if (!X || !Xq8 || !s_x) return MQ_ERR_INVALID_ARG;
-    if (!mq_host::aligned(X, 16) || !mq_host::aligned(Xq8, 16) || !mq_host::aligned(s_x, 2))
-        return MQ_ERR_MISALIGNED;
-    const auto* x = static_cast<const uint16_t*>(X);
-    auto* s = static_cast<uint16_t*>(s_x);
-    const int chunks_per_thread = (K / 16 + kActThreads - 1) / kActThreads;
-    dim3 grid(M), block(kActThreads);
-    if (chunks_per_thread <= 1)
-        hipLaunchKernelGGL(act_quant8_kernel<1>, grid, block, 0, stream, x, M, K, ldx, Xq8, s);
-    else if (chunks_per_thread <= 2)
-        hipLaunchKernelGGL(act_quant8_kernel<2>, grid, block, 0, stream, x, M, K, ldx, Xq8, s);
-    else if (chunks_per_thread <= 4)
-        hipLaunchKernelGGL(act_quant8_kernel<4>, grid, block, 0, stream, x, M, K, ldx, Xq8, s);
-    else if (chunks_per_thread <= 8)
-        hipLaunchKernelGGL(act_quant8_kernel<8>, grid, block, 0, stream, x, M, K, ldx, Xq8, s);
-    else
-        hipLaunchKernelGGL(act_quant8_kernel<0>, grid, block, 0, stream, x, M, K, ldx, Xq8, s);
-    return mq_host::launch_status();
-}
-
-extern "C" mq_status mq_quantize_act(const void* X, int M, int K, int ldx,
-                                     uint8_t* Xq, void* s_x, hipStream_t stream) {
+template <bool A8>
+static mq_status quantize_rows(const void* X, int M, int K, int ldx, uint8_t* Xq, void* s_x, hipStream_t stream) {
     if (M < 0 || K < 0) return MQ_ERR_INVALID_ARG;
     if (M > (1 << 24) || K < 128 || K % 128 != 0 || K > (1 << 20) || ldx < K || ldx % 8 != 0)
         return MQ_ERR_UNSUPPORTED_SHAPE;
@@ -231,19 +170,24 @@ extern "C" mq_status mq_quantize_act(const void* X, int M, int K, int ldx,
         return MQ_ERR_MISALIGNED;
     const auto* x = static_cast<const uint16_t*>(X);
     auto* s = static_cast<uint16_t*>(s_x);
-    const int chunks_per_thread = (K / 16 + kActThreads - 1) / kActThreads;
-    dim3 grid(M), block(kActThreads);
-    if (chunks_per_thread <= 1)
-        hipLaunchKernelGGL(act_quant_kernel<1>, grid, block, 0, stream, x, M, K, ldx, Xq, s);
-    else if (chunks_per_thread <= 2)
-        hipLaunchKernelGGL(act_quant_kernel<2>, grid, block, 0, stream, x, M, K, ldx, Xq, s);
-    else if (chunks_per_thread <= 4)
-        hipLaunchKernelGGL(act_quant_kernel<4>, grid, block, 0, stream, x, M, K, ldx, Xq, s);
-    else if (chunks_per_thread <= 8)
-        hipLaunchKernelGGL(act_quant_kernel<8>, grid, block, 0, stream, x, M, K, ldx, Xq, s);
-    else if (chunks_per_thread <= 16)
-        hipLaunchKernelGGL(act_quant_kernel<16>, grid, block, 0, stream, x, M, K, ldx, Xq, s);
+    const int quarters = K / 32, threads = (quarters + 63) / 64 * 64;
+    if (threads <= kActMaxThreads)
+        hipLaunchKernelGGL((act_quant_kernel<A8, false>), dim3(M), dim3(threads), 0, stream, x, M, K, ldx, Xq, s);
     else
-        hipLaunchKernelGGL(act_quant_kernel<0>, grid, block, 0, stream, x, M, K, ldx, Xq, s);
+        hipLaunchKernelGGL((act_quant_kernel<A8, true>), dim3(M), dim3(kActMaxThreads), 0, stream, x, M, K, ldx, Xq, s);
     return mq_host::launch_status();
+}
+
+}  // namespace mq
+
+using namespace mq;
+
+extern "C" mq_status mq_quantize_act8(const void* X, int M, int K, int ldx,
+                                      uint8_t* Xq8, void* s_x, hipStream_t stream) {
+    return quantize_rows<true>(X, M, K, ldx, Xq8, s_x, stream);
+}
+
+extern "C" mq_status mq_quantize_act(const void* X, int M, int K, int ldx,
+                                     uint8_t* Xq, void* s_x, hipStream_t stream) {
+    return quantize_rows<false>(X, M, K, ldx, Xq, s_x, stream);
 }

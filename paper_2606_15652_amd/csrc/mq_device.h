@@ -279,15 +279,6 @@ __device__ __forceinline__ uint16_t ldg_u16(const void* base, int64_t idx) {
     return reinterpret_cast<const uint16_t*>(base)[idx];
 }
 
-// ----------------------------------------------------------- reductions --
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    for (int off = 32; off > 0; off >>= 1) {
-        uint32_t o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
 }  // namespace mq
 
 // Host-side helpers shared by the API translation units.
