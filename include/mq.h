@@ -204,7 +204,8 @@ mq_status mq_fused_gemm_acc_i32(mq_variant variant, int M, int N, int K,
  * The whole layer from fp16 activations: mq_quantize_act followed by
  * mq_fused_gemm, with the same results bit for bit (Section 4.2 "Kernel
  * Fusion": quantisation fused into the GEMM).  For decode-sized inputs
- * (M <= 4, M * K <= 32768) one kernel does both: every workgroup quantises the
+ * (M <= 4 and M * K <= 32768, or
+ * M <= 8 and M * K <= 24576, 16384 beyond N = 4096) one kernel does both: every workgroup quantises the
  * activation rows into LDS itself, which saves a launch.  Otherwise the
  * activations are quantised into the workspace first.
  *   X, ldx   : fp16 [M, ldx], ldx >= K, ldx % 8 == 0, 16-byte aligned.

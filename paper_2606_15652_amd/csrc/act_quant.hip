@@ -32,67 +32,6 @@ __device__ __forceinline__ int xcd_row(int b, int M) {
     return x * per + min(x, rem) + k;
 }
 
-struct Quarter {
-    uint4 v[4];                                            // 32 fp16
-};
-__device__ __forceinline__ Quarter load_quarter(const uint16_t* p) {
-    Quarter q;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) q.v[i] = reinterpret_cast<const uint4*>(p)[i];
-    return q;
-}
-__device__ __forceinline__ uint32_t quarter_absmax_bits(const Quarter& q) {
-    const uint32_t a = chunk_absmax_bits(q.v[0], q.v[1]), b = chunk_absmax_bits(q.v[2], q.v[3]);
-    return a > b ? a : b;
-}
-
-// Largest v of the wave (v >= 0), by DPP: row shifts, then the row broadcasts
-// that carry a row's maximum on; lane 63 has the result.
-__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
-    auto step = [&](auto ctrl) {
-        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
-        v = o > v ? o : v;
-    };
-    step(std::integral_constant<int, 0x111>{});             // row_shr:1, 2, 4, 8
-    step(std::integral_constant<int, 0x112>{});
-    step(std::integral_constant<int, 0x114>{});
-    step(std::integral_constant<int, 0x118>{});
-    step(std::integral_constant<int, 0x142>{});             // row_bcast:15
-    step(std::integral_constant<int, 0x143>{});             // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// The 32 codes of a quarter as fp32 integers (+0 for zero): quant_mag's steps on
-// the signed value, which hold for qmax = 127 as well: a quotient that is not a
-// tie is at least 2^-13 from one, q1 within 2^-17 of it (2^-24 relative).
-__device__ __forceinline__ void quarter_codes(const Quarter& x, float s, float inv_s, float qmax, float (&q)[32]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t w[4] = {x.v[i].x, x.v[i].y, x.v[i].z, x.v[i].w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float f = half_bits_to_float((uint16_t)(e & 1 ? w[e >> 1] >> 16 : w[e >> 1] & 0xFFFFu));
-            const float q0 = f * inv_s;
-            const float q1 = __builtin_fmaf(__builtin_fmaf(-q0, s, f), inv_s, q0);
-            q[8 * i + e] = __builtin_amdgcn_fmed3f(rintf(q1) + 0.0f, -qmax, qmax);
-        }
-    }
-}
-
-// 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
-// bit 6e; the instruction takes the even codes and the odd ones).
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
-__device__ __forceinline__ u32x6 operand_dwords(const float (&q)[32]) {
-    f32x16 even, odd;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        even[i] = q[2 * i];
-        odd[i] = q[2 * i + 1];
-    }
-    return __builtin_bit_cast(u32x6, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, 8.0f));
-}
-
 // LOOP: rows longer than 32 codes a thread, read a second time for the codes.
 template <bool A8, bool LOOP>
 __global__ __launch_bounds__(kActMaxThreads) void act_quant_kernel(

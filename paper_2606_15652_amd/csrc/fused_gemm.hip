@@ -949,11 +949,22 @@ static int tiled_splits(int M, int N, int K) {
 // When the tiles outnumber a round of resident workgroups, each workgroup
 // takes several in turn (PT), with one item stream running through them.
 // --------------------------------------------------------------------------
-// Fused activation quantisation (FQ): at most kFusedMaxM rows and
-// kFusedCPT 16-element chunks per thread; the workgroup quantises the rows
-// into LDS itself (same arithmetic as mq_quantize_act) instead of reading Xq.
-constexpr int kFusedMaxM = 4, kFusedCPT = 4;
+// Fused activation quantisation (FQ): at most kFusedMaxM rows and kFusedQPT
+// quarters (32 codes) per thread; the workgroup quantises the rows into LDS
+// itself (same arithmetic as mq_quantize_act), in the staged operand form,
+// instead of reading Xq.  Every workgroup repeats that work, so five to eight
+// rows take it for fewer codes: up to kFusedMaxCodes5 where a CU has one
+// workgroup (4096 -> 4096 at M = 5 and 6 7.6 -> 6.8 us against two launches,
+// 3072 -> 4096 at M = 8 7.4 -> 6.5; at 32768 codes, M = 8, 7.7 -> 7.8), up to
+// kFusedMaxCodes5Wide where it may have two (2048 -> 8192 at M = 7 7.6 -> 6.3; at
+// 20480 to 24576 codes 4096 -> 6144 8.7 -> 9.1 to 9.3, 2816 -> 11264 9.5 -> 10.0).
+// With the codes in operand form and a few operations each, one to four rows
+// went 6.1 -> 5.5 us at M = 1, 8.0 -> 6.2 at M = 4 (4096 -> 4096), 31.4 -> 30.1
+// (8192 -> 28672, M = 4).
+constexpr int kFusedMaxM = 8, kFusedQPT = 2;
+constexpr int64_t kFusedMaxCodes = 32768, kFusedMaxCodes5 = 24576, kFusedMaxCodes5Wide = 16384;
 constexpr int kDecodeWaves = 8;
+static_assert(kFusedMaxCodes <= (int64_t)kFusedQPT * 32 * 64 * kDecodeWaves, "every code has a thread");
 
 // Items in flight per wave: stages of WM X fragments, WN B fragments and
 // their scales filling about 96 registers (measured: a deeper ring of the 64 x 64
@@ -970,8 +981,8 @@ struct StreamDepth {
 // a (16 WM WGM) x (16 WN WGN) output tile.  Decode: WM <= 2, WN = 1, 2 or 4
 // (all M <= 32 rows, K over eight waves); medium M: WM = 2 or 4, WN = 4 (the
 // whole 32 x 64 or 64 x 64 tile per wave, K over eight waves).
-// The W4A4 activation operand is read in its stored operand form (main-plane
-// chunk and tail), fused quantisation (FQ) unfolds its codes from LDS.
+// The W4A4 activation operand is in its stored operand form (main-plane chunk
+// and tail), from memory or staged in LDS (XS: copied, FQ: quantised there).
 // A8 (the W4A8 variant): the activation operand is INT8, stored as an e4m3
 // high plane and a folded 4-bit low plane (mq_quantize_act8); each product
 // takes the low-plane MFMA and the fp8 x fp6 MFMA of the high plane chained
@@ -998,8 +1009,8 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
     constexpr bool kScaleShfl = SPW == 4;
     constexpr int kAcc = WM * SPW * 4;                           // sums per lane and accumulator
     // cross-wave partial sums red[wave][value][lane] (one accumulator per
-    // round: raw mode adds the base and then the residual sums); FQ: packed
-    // codes of the M rows (M x K/2 bytes, row-major) in dynamic LDS
+    // round: raw mode adds the base and then the residual sums); XS, FQ: the
+    // operand bytes of the M rows (M x 3K/4) in dynamic LDS
     __shared__ __attribute__((aligned(16))) uint32_t red[NW][kAcc][64];
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
     __shared__ uint32_t amax_sh[kFusedMaxM];
@@ -1066,12 +1077,11 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(FQ ? a.Wq : a.Xq, FQ ? 0u : a.xq_bytes);
     const uint32_t loff = (uint32_t)lrow * kGroupBytes + (uint32_t)lq * 16;   // lane's bytes of a 16-row piece
 
-    // X fragment of rows 16 i .. 16 i + 15 at group g: from the quantised rows
-    // in LDS (FQ; rows past M read 0) or from Xq (rows past M read 0)
+    // X fragment of rows 16 i .. 16 i + 15 at group g from Xq (rows past M read 0)
     auto x_offset = [&](int g, int i) -> uint32_t {
         return ((uint32_t)g * (uint32_t)M + (uint32_t)mw + 16u * i) * kGroupBytes + loff;
     };
-    // XS: the rows' operand bytes copied into LDS at the start, in the
+    // XS, FQ: the rows' operand bytes in LDS from the start, in the
     // layout of Xq except that the 16-byte chunk q of a main-plane row r sits
     // at chunk q ^ ((r / 4) % 4) (the 16 rows of a read then hit distinct
     // banks); rows from M on read row M - 1 (their outputs are not written)
@@ -1085,13 +1095,6 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
             &xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)r) * 32u + (uint32_t)lq * 8u]);
         return act_operand(mv, tv);
     };
-    auto x_lds = [&](int g, int i) -> uint4 {
-        const int row = mw + 16 * i + lrow;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (row < M) v = *reinterpret_cast<const uint4*>(&xs[(int64_t)row * (K / 2) + g * kGroupBytes + lq * 16]);
-        return v;
-    };
-
     f32x4 acc[WM][SPW];
     i32x4 iacc[WM][SPW], racc[WM][SPW];
 #pragma unroll
@@ -1247,9 +1250,9 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
         i32x8 av[WM], ah[A8 ? WM : 1];
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
-            if constexpr (XS) av[i] = x_staged(S.g, i);
+            if constexpr (XS || FQ) av[i] = x_staged(S.g, i);
             else if constexpr (A4) av[i] = act_operand(S.x[i], S.xt[i]);
-            else av[i] = unfold_codes(FQ ? x_lds(S.g, i) : S.x[i]);
+            else av[i] = unfold_codes(S.x[i]);
         }
         if constexpr (A8) {
 #pragma unroll
@@ -1279,23 +1282,19 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
         pin_all();
     };
 
-    // FQ, part 1: this thread's chunks of X, loaded first so that they are
-    // the first loads to land
-    const int nxc = K / 16;
-    uint4 xv[FQ ? kFusedCPT : 1][2];
-    auto row_of = [&](int idx) { return (idx >= nxc) + (idx >= 2 * nxc) + (idx >= 3 * nxc); };
+    // FQ, part 1: this thread's quarters of X (quarter t + 512 i of the rows in
+    // turn), loaded first so that they are the first loads to land
+    const int nq = K / 32;
+    Quarter xv[FQ ? kFusedQPT : 1];
+    int xm[FQ ? kFusedQPT : 1];
     if constexpr (FQ) {
         if (threadIdx.x < kFusedMaxM) amax_sh[threadIdx.x] = 0u;
 #pragma unroll
-        for (int i = 0; i < kFusedCPT; ++i) {
+        for (int i = 0; i < kFusedQPT; ++i) {
             const int idx = (int)threadIdx.x + i * 64 * NW;
-            xv[i][0] = xv[i][1] = make_uint4(0, 0, 0, 0);
-            if (idx < M * nxc) {
-                const int m = row_of(idx), c = idx - m * nxc;
-                const uint16_t* src = a.X + (int64_t)m * a.ldx + 16 * c;
-                xv[i][0] = ldg16(reinterpret_cast<const uint8_t*>(src));
-                xv[i][1] = ldg16(reinterpret_cast<const uint8_t*>(src + 8));
-            }
+            xv[i] = Quarter{};
+            xm[i] = idx / nq;
+            if (idx < M * nq) xv[i] = load_quarter(a.X + (int64_t)xm[i] * a.ldx + 32 * (idx - xm[i] * nq));
         }
     }
 
@@ -1348,33 +1347,35 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
     }
 
     if constexpr (FQ) {
-        // FQ, part 2: row maxima across the workgroup (LDS atomic max on the
-        // sign-cleared fp16 bits), scales, codes into LDS
+        // FQ, part 2: row maxima across the workgroup (on the sign-cleared fp16
+        // bits; a wave whose quarters are all of one row reduces them first, so
+        // that the LDS atomics do not queue on one address), scales, codes
         __syncthreads();                                   // amax_sh cleared
 #pragma unroll
-        for (int i = 0; i < kFusedCPT; ++i) {
-            const int idx = (int)threadIdx.x + i * 64 * NW;
-            if (idx < M * nxc) {
-                const uint32_t c0m = chunk_absmax_bits(xv[i][0]), c1m = chunk_absmax_bits(xv[i][1]);
-                atomicMax(&amax_sh[row_of(idx)], c0m > c1m ? c0m : c1m);
+        for (int i = 0; i < kFusedQPT; ++i) {
+            const uint32_t cm = quarter_absmax_bits(xv[i]);   // 0 past the last quarter
+            const int first = __builtin_amdgcn_readfirstlane(xm[i]), last = __builtin_amdgcn_readlane(xm[i], 63);
+            if (first >= M) continue;
+            if (first == last) {
+                const uint32_t wmax = wave_max_dpp(cm);
+                if (lane == 0) atomicMax(&amax_sh[first], wmax);
+            } else if (xm[i] < M) {
+                atomicMax(&amax_sh[xm[i]], cm);
             }
         }
         __syncthreads();
-        float sc[kFusedMaxM];
+        if ((int)threadIdx.x < M) sx_sh[threadIdx.x] = scale_bits_from_amax(half_bits_to_float((uint16_t)amax_sh[threadIdx.x]));
 #pragma unroll
-        for (int r = 0; r < kFusedMaxM; ++r) {
-            const uint16_t sb = scale_bits_from_amax(half_bits_to_float((uint16_t)amax_sh[r]));
-            sc[r] = half_bits_to_float(sb);
-            if (threadIdx.x == 0) sx_sh[r] = sb;
-        }
-#pragma unroll
-        for (int i = 0; i < kFusedCPT; ++i) {
-            const int idx = (int)threadIdx.x + i * 64 * NW;
-            if (idx < M * nxc) {
-                const int m = row_of(idx), c = idx - m * nxc;
-                const float s = m == 0 ? sc[0] : m == 1 ? sc[1] : m == 2 ? sc[2] : sc[3];
-                *reinterpret_cast<uint2*>(&xs[(int64_t)m * (K / 2) + 8 * c]) =
-                    quant_chunk(xv[i][0], xv[i][1], s, 1.0f / s);
+        for (int i = 0; i < kFusedQPT; ++i) {
+            const int m = xm[i], c = (int)threadIdx.x + i * 64 * NW - m * nq, g = c >> 2, j = c & 3;
+            if (m < M) {
+                const float s = half_bits_to_float(scale_bits_from_amax(half_bits_to_float((uint16_t)amax_sh[m])));
+                float q[32];
+                quarter_codes(xv[i], s, s == 0.0f ? 0.0f : 1.0f / s, (float)kQmax, q);
+                const u32x6 d = operand_dwords(q);
+                *reinterpret_cast<uint4*>(&xs[xs_main(g, m, j)]) = make_uint4(d[0], d[1], d[2], d[3]);
+                *reinterpret_cast<uint2*>(&xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)m) * 32u +
+                                              (uint32_t)j * 8u]) = make_uint2(d[4], d[5]);
             }
         }
         __syncthreads();
@@ -1967,15 +1968,15 @@ extern "C" mq_status mq_fused_gemm_a8_acc_i32(int M, int N, int K,
 // ---------------------------------------------------------------------------
 // Whole layer from fp16 activations
 // ---------------------------------------------------------------------------
-static bool fused_decode_ok(int M, int K) {
-    return M >= 1 && M <= kFusedMaxM && (int64_t)M * (K / 16) <= (int64_t)kFusedCPT * 64 * 8 &&
-           (int64_t)M * (K / 2) <= 64 * 1024;
+static bool fused_decode_ok(int M, int N, int K) {
+    const int64_t most = M <= 4 ? kFusedMaxCodes : N <= 16 * kCUs ? kFusedMaxCodes5 : kFusedMaxCodes5Wide;
+    return M >= 1 && M <= kFusedMaxM && M * (int64_t)K <= most;
 }
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 extern "C" size_t mq_linear_workspace_size(int M, int N, int K) {
-    if (M <= 0 || !mq_host::shape_ok(N, K) || fused_decode_ok(M, K)) return 0;
+    if (M <= 0 || !mq_host::shape_ok(N, K) || fused_decode_ok(M, N, K)) return 0;
     return align256(mq_fused_gemm_workspace_size(M, N, K)) + align256((size_t)M * (K / 4) * 3) +
            align256((size_t)2 * M);
 }
@@ -1996,7 +1997,7 @@ static mq_status linear_impl(int M, int N, int K, const void* X, int ldx,
     if (!mq_host::aligned(s_w, 2) || !mq_host::aligned(Y, 2) || (s_r && !mq_host::aligned(s_r, 2)) ||
         (workspace && !mq_host::aligned(workspace, 16)))
         return MQ_ERR_MISALIGNED;
-    if (fused_decode_ok(M, K)) {
+    if (fused_decode_ok(M, N, K)) {
         GemmArgs a{M, N, K, nullptr, nullptr, Wq, static_cast<const uint16_t*>(s_w),
                    nnzb > 0 ? res_rowptr : nullptr, res_kb, Rq, static_cast<const uint16_t*>(s_r),
                    static_cast<uint16_t*>(Y), ldy, nullptr, nullptr, static_cast<const uint16_t*>(X), ldx};
@@ -2005,7 +2006,7 @@ static mq_status linear_impl(int M, int N, int K, const void* X, int ldx,
         if (st != MQ_OK) return st;
         // (at four rows two strips measured faster than one on the wide
         // layers, where one row takes one: 5120 -> 25600 19.9 -> 19.1 us)
-        launch_decode<1, false, true>(a, M == 1 ? decode_spw_one_row(N) : decode_spw(N), (size_t)M * (K / 2), stream);
+        launch_decode<1, false, true>(a, M == 1 ? decode_spw_one_row(N) : decode_spw(N), (size_t)M * (K / 4) * 3, stream);
         return mq_host::launch_status();
     }
     // quantise into the workspace, then the fused GEMM

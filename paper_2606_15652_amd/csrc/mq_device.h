@@ -16,6 +16,7 @@ constexpr int kQmax = 7;
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- scalars --
 __device__ __forceinline__ float half_bits_to_float(uint16_t b) {
@@ -30,22 +31,6 @@ __device__ __forceinline__ uint16_t float_to_half_bits(float f) {
 // division (-fhip-fp32-correctly-rounded-divide-sqrt, no fast-math).
 __device__ __forceinline__ uint16_t scale_bits_from_amax(float amax, int qmax = kQmax) {
     return float_to_half_bits(amax / (float)qmax);
-}
-
-// |code| of an fp16 x for an fp16 scale s > 0 (the activation quantiser):
-// min(7, round_half_even(|x| / s)), given inv_s = the correctly rounded fp32
-// 1 / s.  x and s are fp16 values, so a
-// quotient that is not a tie lies at least 2^-14 from every half-integer
-// (2|x| - (2k+1) s is a non-zero multiple of the finer of the two exponents'
-// units).  q0 = |x| inv_s is within 2^-20 of |x| / s; one correction step
-// (r = |x| - q0 s is exact: on a tie q0 - (k + 1/2) is a few units of the
-// last place, times s representable) makes q1 exactly k + 1/2 on a tie and
-// keeps it within 2^-22 otherwise, so rint (ties to even) gives the code.
-__device__ __forceinline__ float quant_mag(float ax, float s, float inv_s) {
-    const float q0 = ax * inv_s;
-    const float r = __builtin_fmaf(-q0, s, ax);
-    const float q1 = __builtin_fmaf(r, inv_s, q0);
-    return fminf(rintf(q1), (float)kQmax);
 }
 
 // Code of x for scale s > 0 (inv_s = 1 / s, rounded any way):
@@ -197,43 +182,71 @@ __device__ __forceinline__ uint32_t chunk_absmax_bits(const uint4 v0, const uint
     return m.x > m.y ? m.x : m.y;
 }
 
-// 16 fp16 (two 16-byte loads) -> 16 codes for scale s (inv_s = 1 / s) -> one
-// folded chunk.  Each 6-bit field is the code's magnitude with x's sign bit
-// at bit 5 when the code is not zero (as fold_codes writes it), laid out at
-// bit 6e of the 96-bit word and folded.
-__device__ __forceinline__ uint32_t code_field(uint32_t h16, float s, float inv_s) {
-    // quant_mag's steps on the signed value (every step is sign-symmetric);
-    // adding +0 turns a negative zero into +0, so the sign bit of q is set
-    // exactly for the negative codes
-    const float x = half_bits_to_float((uint16_t)h16);
-    const float q0 = x * inv_s;
-    const float r = __builtin_fmaf(-q0, s, x);
-    const float q = rintf(__builtin_fmaf(r, inv_s, q0)) + 0.0f;
-    const uint32_t m = min((uint32_t)fabsf(q), (uint32_t)kQmax);
-    return m | ((__float_as_uint(q) >> 31) << 5);
-}
-// 16 fp16 -> the 96-bit word (o0, o1, o2) of their 6-bit code fields
-__device__ __forceinline__ void quant_fields(const uint4 v0, const uint4 v1, float s, float inv_s,
-                                             uint32_t& o0, uint32_t& o1, uint32_t& o2) {
-    if (s == 0.0f) {
-        o0 = o1 = o2 = 0u;
-        return;
-    }
-    const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-    uint32_t f[16];
+struct Quarter {
+    uint4 v[4];                                            // 32 fp16
+};
+__device__ __forceinline__ Quarter load_quarter(const uint16_t* p) {
+    Quarter q;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        f[2 * i] = code_field(w[i] & 0xFFFFu, s, inv_s);
-        f[2 * i + 1] = code_field(w[i] >> 16, s, inv_s);
-    }
-    o0 = f[0] | (f[1] << 6) | (f[2] << 12) | (f[3] << 18) | (f[4] << 24) | (f[5] << 30);
-    o1 = (f[5] >> 2) | (f[6] << 4) | (f[7] << 10) | (f[8] << 16) | (f[9] << 22) | (f[10] << 28);
-    o2 = (f[10] >> 4) | (f[11] << 2) | (f[12] << 8) | (f[13] << 14) | (f[14] << 20) | (f[15] << 26);
+    for (int i = 0; i < 4; ++i) q.v[i] = reinterpret_cast<const uint4*>(p)[i];
+    return q;
 }
-__device__ __forceinline__ uint2 quant_chunk(const uint4 v0, const uint4 v1, float s, float inv_s) {
-    uint32_t o0, o1, o2;
-    quant_fields(v0, v1, s, inv_s, o0, o1, o2);
-    return make_uint2(o0 | (o2 & kFoldA), o1 | (o2 & kFoldB));
+__device__ __forceinline__ uint32_t quarter_absmax_bits(const Quarter& q) {
+    const uint32_t a = chunk_absmax_bits(q.v[0], q.v[1]), b = chunk_absmax_bits(q.v[2], q.v[3]);
+    return a > b ? a : b;
+}
+
+// Largest v of the wave (v >= 0), by DPP: row shifts, then the row broadcasts
+// that carry a row's maximum on; lane 63 has the result.
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
+    auto step = [&](auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
+        v = o > v ? o : v;
+    };
+    step(std::integral_constant<int, 0x111>{});             // row_shr:1, 2, 4, 8
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});             // row_bcast:15
+    step(std::integral_constant<int, 0x143>{});             // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The 32 codes of a quarter as fp32 integers (+0 for zero): clamp(round_half_even(
+// x / s), -qmax, qmax), given inv_s = the correctly rounded fp32 1 / s (0 for a
+// zero scale: all codes 0).  x and s are fp16 values, so a quotient that is not
+// a tie lies at least 2^-14 from every half-integer (2|x| - (2k+1) s is a
+// non-zero multiple of the finer of the two exponents' units).  q0 = x inv_s is
+// within a few units of the last place of x / s; one correction step
+// (r = x - q0 s is exact: on a tie q0 - (k + 1/2) is a few units of the
+// last place, times s representable) makes q1 exactly k + 1/2 on a tie and
+// keeps it within 2^-24 (relative, at most 2^-17 for qmax = 127) otherwise, so
+// rint (ties to even) gives the code.
+__device__ __forceinline__ void quarter_codes(const Quarter& x, float s, float inv_s, float qmax, float (&q)[32]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t w[4] = {x.v[i].x, x.v[i].y, x.v[i].z, x.v[i].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float f = half_bits_to_float((uint16_t)(e & 1 ? w[e >> 1] >> 16 : w[e >> 1] & 0xFFFFu));
+            const float q0 = f * inv_s;
+            const float q1 = __builtin_fmaf(__builtin_fmaf(-q0, s, f), inv_s, q0);
+            q[8 * i + e] = __builtin_amdgcn_fmed3f(rintf(q1) + 0.0f, -qmax, qmax);
+        }
+    }
+}
+
+// 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
+// bit 6e; the instruction takes the even codes and the odd ones).
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+__device__ __forceinline__ u32x6 operand_dwords(const float (&q)[32]) {
+    f32x16 even, odd;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        even[i] = q[2 * i];
+        odd[i] = q[2 * i + 1];
+    }
+    return __builtin_bit_cast(u32x6, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, 8.0f));
 }
 
 // ----------------------------------------------------- device group order --
