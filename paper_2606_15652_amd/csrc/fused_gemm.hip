@@ -118,7 +118,8 @@ __device__ __forceinline__ void group_row(const i32x8 a, const i32x8 (&w)[WN], c
 // --------------------------------------------------------------------------
 // Workgroup: 2 x WAVES_N waves owning a (32 WMB) x (64 WAVES_N) output tile:
 // <8, 4> is 256 x 256 with eight waves, one workgroup per CU; <4, 2> is
-// 128 x 128 with four waves, two per CU.  Wave (wm, wn) owns WMB sub-tile
+// 128 x 128 with four waves, two per CU; <4, 4>, 128 x 256, is the W4A8 tile.
+// Wave (wm, wn) owns WMB sub-tile
 // rows of 16 and four 16-column sub-tiles at tile columns 16 (wn + WAVES_N c),
 // interleaved so that every wave has sub-tiles in each 128-column residual
 // block row of the tile.
@@ -134,8 +135,9 @@ __device__ __forceinline__ void group_row(const i32x8 a, const i32x8 (&w)[WN], c
 // after it.  The DMA does not raise the compiler's wait counters, so the
 // kernel waits on the vector-memory counter itself (wait_loads_and_sync).
 //
-// Loads use per-tile buffer resources over operands in device group order, so
-// each load instruction reads 1 KB of whole 64-byte rows, contiguous.  16-byte
+// Loads go through whole-operand buffer resources over operands in device group
+// order, so each load instruction reads 1 KB of whole 64-byte rows, contiguous
+// (scalar offsets step from group to group).  16-byte
 // chunks are XOR-swizzled by (row >> 1) & 3 inside 64-byte rows, which makes
 // the 16-lane fragment reads conflict-free (LDS serves 8 lanes of 16 B per
 // 128-byte bank window).
