@@ -58,12 +58,15 @@ __global__ __launch_bounds__(kActMaxThreads) void act_quant_kernel(
 
     constexpr int qmax = A8 ? kQmax8 : kQmax;
     const uint16_t sb = scale_bits_from_amax(half_bits_to_float((uint16_t)amax), qmax);
-    const float s = half_bits_to_float(sb);
-    const float inv_s = s == 0.0f ? 0.0f : 1.0f / s;        // a zero scale: all codes 0
+    float s = half_bits_to_float(sb);
+    float inv_s = s == 0.0f ? 0.0f : 1.0f / s;              // a zero scale: all codes 0
     if (t == 0) s_x[m] = sb;
+    const bool finite = amax < kHalfInf;
+    if (!finite) nonfinite_scale<A8>(s, inv_s);
 
     for (int c = t; c < nq; c += threads) {
         if constexpr (LOOP) v = load_quarter(row + 32 * c);
+        if (!finite) nonfinite_quarter<A8>(v, amax);
         float q[32];
         quarter_codes(v, s, inv_s, (float)qmax, q);
         const int g = c >> 2, j = c & 3;                    // quarter j of group g

@@ -1371,9 +1371,15 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
         for (int i = 0; i < kFusedQPT; ++i) {
             const int m = xm[i], c = (int)threadIdx.x + i * 64 * NW - m * nq, g = c >> 2, j = c & 3;
             if (m < M) {
-                const float s = half_bits_to_float(scale_bits_from_amax(half_bits_to_float((uint16_t)amax_sh[m])));
+                const uint32_t amax = amax_sh[m];
+                float s = half_bits_to_float(scale_bits_from_amax(half_bits_to_float((uint16_t)amax)));
+                float inv_s = s == 0.0f ? 0.0f : 1.0f / s;
+                if (amax >= kHalfInf) {
+                    nonfinite_scale<false>(s, inv_s);
+                    nonfinite_quarter<false>(xv[i], amax);
+                }
                 float q[32];
-                quarter_codes(xv[i], s, s == 0.0f ? 0.0f : 1.0f / s, (float)kQmax, q);
+                quarter_codes(xv[i], s, inv_s, (float)kQmax, q);
                 const u32x6 d = operand_dwords(q);
                 *reinterpret_cast<uint4*>(&xs[xs_main(g, m, j)]) = make_uint4(d[0], d[1], d[2], d[3]);
                 *reinterpret_cast<uint2*>(&xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)m) * 32u +

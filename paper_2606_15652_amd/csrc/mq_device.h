@@ -236,6 +236,26 @@ __device__ __forceinline__ void quarter_codes(const Quarter& x, float s, float i
     }
 }
 
+// A row whose largest |x| (its fp16 bits, amax) is infinite or NaN: its scale is
+// that value, and no quotient is a code.  INT4: all codes are 0 (so the outputs
+// are NaN, infinity times an exact zero).  INT8: 0 for the finite values beside
+// an infinity, -127 for the others and throughout a row with a NaN.  x is
+// replaced by values that the steps of quarter_codes take to these codes with
+// the scale of nonfinite_scale.
+constexpr uint32_t kHalfInf = 0x7C00u;
+template <bool A8>
+__device__ __forceinline__ void nonfinite_scale(float& s, float& inv_s) {
+    s = A8 ? 0x1p-7f : 0.0f;
+    inv_s = A8 ? 0x1p7f : 0.0f;                            // -1 is clamped to -127
+}
+template <bool A8>
+__device__ __forceinline__ void nonfinite_quarter(Quarter& x, uint32_t amax) {
+    auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0xBC00u : 0u; };
+    auto two = [&](uint32_t w) { return A8 ? one(w & 0xFFFFu) | (one(w >> 16) << 16) : 0u; };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x.v[i] = make_uint4(two(x.v[i].x), two(x.v[i].y), two(x.v[i].z), two(x.v[i].w));
+}
+
 // 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
 // bit 6e; the instruction takes the even codes and the odd ones).
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));

@@ -7,7 +7,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
-from gpu_util import _announce, dev, half_bits, host, mq, tc  # noqa: F401
+from gpu_util import _announce, dev, gpu_pw, half_bits, host, mq, random_operands, tc  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +45,34 @@ def test_quantisers_bit_exact(tc, mq, orc, M, K):
     assert np.array_equal(orc.packed_from_act6(host(Xq), K), q4)
     assert np.array_equal(host(codes8), q8)
     assert np.array_equal(host(again), host(Xq8))       # every layout byte, zeros of either sign as +0
+
+
+@pytest.mark.parametrize("K,N", [(128, 128), (1024, 256), (8192, 128), (32896, 128)])
+def test_rows_with_infinities_and_nans(tc, mq, orc, K, N):
+    """A row with an infinity has an infinite scale and INT4 codes 0, so its
+    outputs are NaN; its INT8 codes are -127 where x is infinite and 0
+    elsewhere.  A row with a NaN has a NaN scale and outputs, INT4 codes 0 and
+    INT8 codes -127.  The rows beside them are as without it."""
+    x = _rows(8, K)
+    x[1, 5], x[2, K - 1], x[5, 7] = np.inf, -np.inf, np.nan
+    x[6] = -np.inf
+    x[7, 3], x[7, K // 2] = np.inf, -np.nan
+    d = dev(tc, x)
+    Xq, s4 = mq.quantize_act(d)
+    Xq8, s8 = mq.quantize_act8(d)
+    q4, q8 = host(mq.unpack_act(Xq)), host(mq.unpack_act8(Xq8))
+    for s in (host(s4), host(s8)):
+        assert np.array_equal(np.isinf(s), [0, 1, 1, 0, 0, 0, 1, 0]) and np.array_equal(np.isnan(s), [0, 0, 0, 0, 0, 1, 0, 1])
+    bad = [1, 2, 5, 6, 7]
+    assert not q4[bad].any()
+    nan_row = np.isnan(x).any(1)
+    want8 = np.where(nan_row[:, None] | ~np.isfinite(x), -127, 0)
+    assert np.array_equal(q8[bad], want8[bad])
+    good = [0, 3, 4]
+    assert np.array_equal(q8[good], orc.quantize_act8(x[good])[0])
+    ops = random_operands(1, N, K, 1, seed=K)
+    pw = gpu_pw(tc, mq, N, K, *ops[2:6], *ops[7:])
+    for rows in ([1], [0, 1, 2, 3], [4, 5, 6, 7], list(range(8))):      # one kernel at few codes, two otherwise
+        Y = host(mq.linear(d[rows].contiguous(), pw))
+        assert np.array_equal(np.isnan(Y).all(1), [r in bad for r in rows])
+        assert np.array_equal(np.isnan(Y).any(1), [r in bad for r in rows])
