@@ -138,6 +138,9 @@ __global__ __launch_bounds__(kPrepThreads) void quant_base_kernel(
 // ---------------------------------------------------------------------------
 constexpr int kHessThreads = 512, kHessCols = 64, kHessRows = 256;
 constexpr int kHessVecs = kHessRows * kHessCols / 8 / kHessThreads;   // 8-channel pieces a thread and step
+__host__ __device__ constexpr int hess_steps(int T) { return (T - 1) / kHessRows + 1; }   // T >= 1
+static_assert(hess_steps(1) == 1 && hess_steps(kHessRows + 1) == 2 && hess_steps(0x7fffffff) == 1 << 23,
+              "no token count overflows the step count");
 
 template <bool VEC>
 __global__ __launch_bounds__(kHessThreads) void hessian_diag_kernel(
@@ -183,7 +186,7 @@ __global__ __launch_bounds__(kHessThreads) void hessian_diag_kernel(
             dst[1] = make_float4(f[4], f[5], f[6], f[7]);
         }
     };
-    const int steps = (T + kHessRows - 1) / kHessRows;
+    const int steps = hess_steps(T);
     Piece d[kHessVecs];
     fetch(0, d);
     put(0, d);
