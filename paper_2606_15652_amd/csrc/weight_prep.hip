@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kPrepThreads) void quant_base_kernel(
 // whole 128-byte lines) and put their squares -- exact in fp32 -- into LDS,
 // and wave 0 adds the rows of the step before, one channel a lane.  (One thread
 // per channel, each load waited for: 484 us at T = 2048, K = 4096; this takes
-// 21 us.)
+// 19 us.)
 // ---------------------------------------------------------------------------
 constexpr int kHessThreads = 512, kHessCols = 64, kHessRows = 256;
 constexpr int kHessVecs = kHessRows * kHessCols / 8 / kHessThreads;   // 8-channel pieces a thread and step
@@ -198,9 +198,13 @@ __global__ __launch_bounds__(kHessThreads) void hessian_diag_kernel(
             put((s + 1) & 1, d);
             fetch(s + 2, d);
         }
-        if (t < 64) {                                     // tokens past T are zeros: adding them changes nothing
-#pragma unroll 16
-            for (int r = 0; r < kHessRows; ++r) acc += (double)sq[s & 1][r][lane];
+        if (t < 64) {
+            // sixteens of rows that hold tokens (all 256 rows of the last step took 3.9 us at T = 1
+            // instead of 2.4, 6.5 instead of 4.8 at T = 257); rows past T are zeros, which change nothing
+            const int rows = s + 1 < steps ? kHessRows : T - s * kHessRows;
+            for (int r0 = 0; r0 < rows; r0 += 16)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc += (double)sq[s & 1][r0 + r][lane];
         }
         __syncthreads();
     }

@@ -51,6 +51,16 @@ def test_select_blocks_matches_a_stable_sort(tc, mq, kind, NB, KB):
 def test_hessian_diag_is_the_sequential_sum(tc, mq, T, K, ldx, offset):
     """fp16 values over many binades (some partial sums round, so the order of
     the additions shows)."""
+    _check_hessian(tc, mq, T, K, ldx, offset)
+
+
+# tokens that fill whole sixteens of the last step, and one more or less
+@pytest.mark.parametrize("T", [8, 15, 16, 17, 31, 271, 272, 273])
+def test_hessian_diag_last_step(tc, mq, T):
+    _check_hessian(tc, mq, T, 72, 72, 0)
+
+
+def _check_hessian(tc, mq, T, K, ldx, offset):
     rng = np.random.default_rng(T + K)
     buf = (rng.standard_normal(T * ldx + 8) * 2.0 ** rng.integers(-9, 10, T * ldx + 8)).astype(np.float16)
     x = np.lib.stride_tricks.as_strided(buf[offset:], (T, K), (2 * ldx, 2)).astype(np.float64)
