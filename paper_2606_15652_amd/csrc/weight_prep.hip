@@ -252,32 +252,36 @@ __global__ __launch_bounds__(kPrepThreads) void score_dhessian_kernel(
 
 // ---------------------------------------------------------------------------
 // Top-K selection: the nnzb blocks of largest score, ties to the lower linear
-// index, as a CSR.  One workgroup of 1024 threads:
+// index, as a CSR.  One workgroup:
 //   1. a most-significant-digit radix search over order-preserving 64-bit keys
-//      (11-bit digits, from the first bit in which the keys differ) narrows
-//      [lo, lo + 2^bits) to the keys that hold the nnzb-th largest, and stops
-//      as soon as all of them are taken;
+//      (digits of log2(2 kSelThreads) bits, from the first bit in which the keys
+//      differ) narrows [lo, lo + 2^bits) to the keys that hold the nnzb-th
+//      largest, and stops as soon as all of them are taken;
 //   2. one pass in linear order (block rows are consecutive): a block is
 //      selected when its key is above that range, or in it and among the first
 //      `need` of those; a block-wide scan of both counts gives every selected
 //      block its place and every block row its start.
 // It reads the scores once when they fit in registers (kSelItems a thread),
-// else once per digit.  Bound by latency: a few barriers a digit; typical
-// scores take two or three digits.  (Counting each block's rank against all
-// scores, twice, took 2 x 292 us for 112 x 32 blocks; this takes 18 us.)
+// else once per digit.  Bound by one CU's instruction issue and a few barriers
+// a digit (typical scores take two or three digits), so few blocks take
+// threads and code for no more items than they have: with 1024 threads of 16
+// items for every size, 1 block took 9.9 us against 2.5 with <64, 1>, 1024
+// blocks 12.6 against 8.0 with <1024, 1>, 3584 14.2 against 9.7 with <1024, 4>.
+// (Counting each block's rank against all scores, twice, takes 4.9, 174 and
+// 600 us for these.)
 // ---------------------------------------------------------------------------
-constexpr int kSelThreads = 1024, kSelItems = 16, kSelDigit = 11;
-constexpr int kSelBins = 1 << kSelDigit, kSelWaves = kSelThreads / 64;
-
 // order-preserving key of a finite score (-0 as +0)
 __device__ __forceinline__ uint64_t score_key(double s) {
     const uint64_t u = (uint64_t)__double_as_longlong(s + 0.0);
     return (u >> 63) ? ~u : u | (1ull << 63);
 }
 
+template <int kSelThreads, int kSelItems>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const double* __restrict__ score, int NB, int KB, int nnzb,
     int32_t* __restrict__ rowptr, int32_t* __restrict__ kb_out) {
+    constexpr int kSelBins = 2 * kSelThreads, kSelWaves = kSelThreads / 64;
+    constexpr int kSelDigit = 31 - __builtin_clz(kSelBins);
     __shared__ int hist[kSelBins];
     __shared__ uint64_t lo_sh[kSelWaves], hi_sh[kSelWaves];
     __shared__ int wsum[2][kSelWaves];
@@ -290,7 +294,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     // item i < items of tile b: linear index (b kSelThreads + t) items + i
     const int items = min(kSelItems, (n + kSelThreads - 1) / kSelThreads);
     const int tiles = (n + kSelThreads * items - 1) / (kSelThreads * items);
-    auto index = [&](int b, int i) { return ((int64_t)b * kSelThreads + t) * items + i; };
+    auto index = [&](int b, int i) { return (b * kSelThreads + t) * items + i; };      // below 2^24 + 2^14
     auto valid = [&](int b, int i) { return i < items && index(b, i) < n; };
     uint64_t key[kSelItems];
     auto load_tile = [&](int b) {
@@ -403,8 +407,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
             base_gt += wsum[0][w];
             base_eq += wsum[1][w];
         }
-        const int64_t idx0 = index(b, 0);
-        int row = (int)(idx0 / KB), col = (int)(idx0 % KB);
+        const int idx0 = index(b, 0);
+        int row = idx0 / KB, col = idx0 - row * KB;
 #pragma unroll
         for (int i = 0; i < kSelItems; ++i) {
             if (valid(b, i)) {
@@ -525,7 +529,14 @@ extern "C" mq_status mq_select_blocks(const double* score, int NB, int KB, int n
     if (!mq_host::aligned(score, 8) || !mq_host::aligned(res_rowptr, 4) ||
         (res_kb && !mq_host::aligned(res_kb, 4)))
         return MQ_ERR_MISALIGNED;
-    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(kSelThreads), 0, stream, score, NB, KB, nnzb, res_rowptr, res_kb);
+    const int n = NB * KB;
+    auto run = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, stream, score, NB, KB, nnzb, res_rowptr, res_kb);
+    };
+    if (n <= 64) run(select_kernel<64, 1>, 64);
+    else if (n <= 1024) run(select_kernel<1024, 1>, 1024);
+    else if (n <= 4096) run(select_kernel<1024, 4>, 1024);
+    else run(select_kernel<1024, 16>, 1024);
     return mq_host::launch_status();
 }
 

@@ -31,6 +31,17 @@ def _scores(kind, NB, KB, rng):
 @pytest.mark.parametrize("kind", ["normal", "ties", "equal", "lastbit"])
 @pytest.mark.parametrize("NB,KB", [(1, 1), (3, 7), (33, 32), (128, 128), (129, 127), (1, 16385), (300, 200)])
 def test_select_blocks_matches_a_stable_sort(tc, mq, kind, NB, KB):
+    _check_selection(tc, mq, kind, NB, KB)
+
+
+# the largest and the next block count of each instantiation of the kernel
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "lastbit"])
+@pytest.mark.parametrize("NB,KB", [(7, 9), (8, 8), (5, 13), (32, 32), (25, 41), (64, 64), (17, 241)])
+def test_select_blocks_at_the_split_edges(tc, mq, kind, NB, KB):
+    _check_selection(tc, mq, kind, NB, KB)
+
+
+def _check_selection(tc, mq, kind, NB, KB):
     rng = np.random.default_rng(NB * 1000 + KB)
     score = _scores(kind, NB, KB, rng)
     n = NB * KB
