@@ -1287,16 +1287,16 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
     // FQ, part 1: this thread's quarters of X (quarter t + 512 i of the rows in
     // turn), loaded first so that they are the first loads to land
     const int nq = K / 32;
-    Quarter xv[FQ ? kFusedQPT : 1];
+    Halves<32> xv[FQ ? kFusedQPT : 1];
     int xm[FQ ? kFusedQPT : 1];
     if constexpr (FQ) {
         if (threadIdx.x < kFusedMaxM) amax_sh[threadIdx.x] = 0u;
 #pragma unroll
         for (int i = 0; i < kFusedQPT; ++i) {
             const int idx = (int)threadIdx.x + i * 64 * NW;
-            xv[i] = Quarter{};
+            xv[i] = Halves<32>{};
             xm[i] = idx / nq;
-            if (idx < M * nq) xv[i] = load_quarter(a.X + (int64_t)xm[i] * a.ldx + 32 * (idx - xm[i] * nq));
+            if (idx < M * nq) xv[i] = load_halves<32>(a.X + (int64_t)xm[i] * a.ldx + 32 * (idx - xm[i] * nq));
         }
     }
 
@@ -1355,7 +1355,7 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
         __syncthreads();                                   // amax_sh cleared
 #pragma unroll
         for (int i = 0; i < kFusedQPT; ++i) {
-            const uint32_t cm = quarter_absmax_bits(xv[i]);   // 0 past the last quarter
+            const uint32_t cm = absmax_bits(xv[i]);   // 0 past the last quarter
             const int first = __builtin_amdgcn_readfirstlane(xm[i]), last = __builtin_amdgcn_readlane(xm[i], 63);
             if (first >= M) continue;
             if (first == last) {
@@ -1376,10 +1376,10 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
                 float inv_s = s == 0.0f ? 0.0f : 1.0f / s;
                 if (amax >= kHalfInf) {
                     nonfinite_scale<false>(s, inv_s);
-                    nonfinite_quarter<false>(xv[i], amax);
+                    nonfinite_values<false>(xv[i], amax);
                 }
                 float q[32];
-                quarter_codes(xv[i], s, inv_s, (float)kQmax, q);
+                quant_codes(xv[i], s, inv_s, (float)kQmax, q);
                 const u32x6 d = operand_dwords(q);
                 *reinterpret_cast<uint4*>(&xs[xs_main(g, m, j)]) = make_uint4(d[0], d[1], d[2], d[3]);
                 *reinterpret_cast<uint2*>(&xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)m) * 32u +

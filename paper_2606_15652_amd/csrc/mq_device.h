@@ -16,6 +16,7 @@ constexpr int kQmax = 7;
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------- scalars --
@@ -182,18 +183,27 @@ __device__ __forceinline__ uint32_t chunk_absmax_bits(const uint4 v0, const uint
     return m.x > m.y ? m.x : m.y;
 }
 
-struct Quarter {
-    uint4 v[4];                                            // 32 fp16
+// C consecutive fp16 values of a row: a quarter of a group (32), or half of one.
+template <int C>
+struct Halves {
+    static_assert(C == 32 || C == 16, "a quarter or half of one");
+    uint4 v[C / 8];
 };
-__device__ __forceinline__ Quarter load_quarter(const uint16_t* p) {
-    Quarter q;
+template <int C>
+__device__ __forceinline__ Halves<C> load_halves(const uint16_t* p) {
+    Halves<C> x;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) q.v[i] = reinterpret_cast<const uint4*>(p)[i];
-    return q;
+    for (int i = 0; i < C / 8; ++i) x.v[i] = reinterpret_cast<const uint4*>(p)[i];
+    return x;
 }
-__device__ __forceinline__ uint32_t quarter_absmax_bits(const Quarter& q) {
-    const uint32_t a = chunk_absmax_bits(q.v[0], q.v[1]), b = chunk_absmax_bits(q.v[2], q.v[3]);
-    return a > b ? a : b;
+template <int C>
+__device__ __forceinline__ uint32_t absmax_bits(const Halves<C>& x) {
+    uint32_t m = chunk_absmax_bits(x.v[0], x.v[1]);
+    if constexpr (C == 32) {
+        const uint32_t n = chunk_absmax_bits(x.v[2], x.v[3]);
+        m = n > m ? n : m;
+    }
+    return m;
 }
 
 // Largest v of the wave (v >= 0), by DPP: row shifts, then the row broadcasts
@@ -212,7 +222,7 @@ __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// The 32 codes of a quarter as fp32 integers (+0 for zero): clamp(round_half_even(
+// The codes of C values as fp32 integers (+0 for zero): clamp(round_half_even(
 // x / s), -qmax, qmax), given inv_s = the correctly rounded fp32 1 / s (0 for a
 // zero scale: all codes 0).  x and s are fp16 values, so a quotient that is not
 // a tie lies at least 2^-14 from every half-integer (2|x| - (2k+1) s is a
@@ -222,9 +232,10 @@ __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
 // last place, times s representable) makes q1 exactly k + 1/2 on a tie and
 // keeps it within 2^-24 (relative, at most 2^-17 for qmax = 127) otherwise, so
 // rint (ties to even) gives the code.
-__device__ __forceinline__ void quarter_codes(const Quarter& x, float s, float inv_s, float qmax, float (&q)[32]) {
+template <int C>
+__device__ __forceinline__ void quant_codes(const Halves<C>& x, float s, float inv_s, float qmax, float (&q)[C]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < C / 8; ++i) {
         const uint32_t w[4] = {x.v[i].x, x.v[i].y, x.v[i].z, x.v[i].w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -240,7 +251,7 @@ __device__ __forceinline__ void quarter_codes(const Quarter& x, float s, float i
 // that value, and no quotient is a code.  INT4: all codes are 0 (so the outputs
 // are NaN, infinity times an exact zero).  INT8: 0 for the finite values beside
 // an infinity, -127 for the others and throughout a row with a NaN.  x is
-// replaced by values that the steps of quarter_codes take to these codes with
+// replaced by values that the steps of quant_codes take to these codes with
 // the scale of nonfinite_scale.
 constexpr uint32_t kHalfInf = 0x7C00u;
 template <bool A8>
@@ -248,16 +259,17 @@ __device__ __forceinline__ void nonfinite_scale(float& s, float& inv_s) {
     s = A8 ? 0x1p-7f : 0.0f;
     inv_s = A8 ? 0x1p7f : 0.0f;                            // -1 is clamped to -127
 }
-template <bool A8>
-__device__ __forceinline__ void nonfinite_quarter(Quarter& x, uint32_t amax) {
+template <bool A8, int C>
+__device__ __forceinline__ void nonfinite_values(Halves<C>& x, uint32_t amax) {
     auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0xBC00u : 0u; };
     auto two = [&](uint32_t w) { return A8 ? one(w & 0xFFFFu) | (one(w >> 16) << 16) : 0u; };
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x.v[i] = make_uint4(two(x.v[i].x), two(x.v[i].y), two(x.v[i].z), two(x.v[i].w));
+    for (int i = 0; i < C / 8; ++i) x.v[i] = make_uint4(two(x.v[i].x), two(x.v[i].y), two(x.v[i].z), two(x.v[i].w));
 }
 
 // 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
-// bit 6e; the instruction takes the even codes and the odd ones).
+// bit 6e; the instruction takes the even codes and the odd ones); 16 codes ->
+// three dwords, d[0 .. 2] (the instruction's other inputs are not set).
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 __device__ __forceinline__ u32x6 operand_dwords(const float (&q)[32]) {
     f32x16 even, odd;
@@ -267,6 +279,18 @@ __device__ __forceinline__ u32x6 operand_dwords(const float (&q)[32]) {
         odd[i] = q[2 * i + 1];
     }
     return __builtin_bit_cast(u32x6, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, 8.0f));
+}
+__device__ __forceinline__ u32x6 operand_dwords(const float (&q)[16]) {
+    f32x8 even, odd;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        even[i] = q[2 * i];
+        odd[i] = q[2 * i + 1];
+    }
+    auto widen = [](f32x8 v) {
+        return __builtin_shufflevector(v, v, 0, 1, 2, 3, 4, 5, 6, 7, -1, -1, -1, -1, -1, -1, -1, -1);
+    };
+    return __builtin_bit_cast(u32x6, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(widen(even), widen(odd), 8.0f));
 }
 
 // ----------------------------------------------------- device group order --

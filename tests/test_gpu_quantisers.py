@@ -32,6 +32,18 @@ def _rows(M, K):
 
 @pytest.mark.parametrize("M,K", [(1, 128), (13, 2176), (31, 4096), (7, 32768), (7, 32896), (300, 1024), (64, 8192)])
 def test_quantisers_bit_exact(tc, mq, orc, M, K):
+    _check_quantisers(tc, mq, orc, M, K)
+
+
+# both sides of every line between the splits: half a quarter or a quarter a
+# thread (by rows and length), one, two or more pieces a thread
+@pytest.mark.parametrize("M,K", [(9000, 128), (1300, 1024), (70, 1152), (256, 2048), (257, 2048), (1024, 2176), (1025, 2176),
+                                 (9, 8192), (9, 8320), (3, 16384), (7, 65536), (7, 65664)])
+def test_quantisers_at_the_split_edges(tc, mq, orc, M, K):
+    _check_quantisers(tc, mq, orc, M, K)
+
+
+def _check_quantisers(tc, mq, orc, M, K):
     x = _rows(M, K)
     d = dev(tc, x)
     Xq, s4 = mq.quantize_act(d)
@@ -47,7 +59,7 @@ def test_quantisers_bit_exact(tc, mq, orc, M, K):
     assert np.array_equal(host(again), host(Xq8))       # every layout byte, zeros of either sign as +0
 
 
-@pytest.mark.parametrize("K,N", [(128, 128), (1024, 256), (8192, 128), (32896, 128)])
+@pytest.mark.parametrize("K,N", [(128, 128), (1024, 256), (8192, 128), (16384, 128), (32896, 128), (65664, 128)])
 def test_rows_with_infinities_and_nans(tc, mq, orc, K, N):
     """A row with an infinity has an infinite scale and INT4 codes 0, so its
     outputs are NaN; its INT8 codes are -127 where x is infinite and 0
