@@ -32,6 +32,7 @@
 
 #include <stddef.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -951,22 +952,32 @@ static int tiled_splits(int M, int N, int K) {
 // When the tiles outnumber a round of resident workgroups, each workgroup
 // takes several in turn (PT), with one item stream running through them.
 // --------------------------------------------------------------------------
-// Fused activation quantisation (FQ): at most kFusedMaxM rows and kFusedQPT
-// quarters (32 codes) per thread; the workgroup quantises the rows into LDS
+// Fused activation quantisation (FQ: codes a thread takes at a time, 32 or 16;
+// 0: none): at most kFusedMaxM rows and kFusedQPT
+// quarters (32 codes) or one half of a quarter per thread; the workgroup quantises the rows into LDS
 // itself (same arithmetic as mq_quantize_act), in the staged operand form,
 // instead of reading Xq.  Every workgroup repeats that work, so five to eight
 // rows take it for fewer codes: up to kFusedMaxCodes5 where a CU has one
 // workgroup (4096 -> 4096 at M = 5 and 6 7.6 -> 6.8 us against two launches,
 // 3072 -> 4096 at M = 8 7.4 -> 6.5; at 32768 codes, M = 8, 7.7 -> 7.8), up to
-// kFusedMaxCodes5Wide where it may have two (2048 -> 8192 at M = 7 7.6 -> 6.3; at
+// kFusedMaxCodes5Wide where it may have two or takes several tiles (2048 -> 8192
+// at M = 7 7.6 -> 6.3, 2048 -> 28672 at M = 8 10.4 -> 10.2, 2048 -> 51200 16.4 -> 15.7,
+// the least 2048 -> 20480 at M = 7 and 8, 8.75 -> 8.8 to 9.0; at
 // 20480 to 24576 codes 4096 -> 6144 8.7 -> 9.1 to 9.3, 2816 -> 11264 9.5 -> 10.0).
 // With the codes in operand form and a few operations each, one to four rows
 // went 6.1 -> 5.5 us at M = 1, 8.0 -> 6.2 at M = 4 (4096 -> 4096), 31.4 -> 30.1
 // (8192 -> 28672, M = 4).
+// A thread's 32 codes are about 0.4 us of one wave's instructions, which two
+// workgroups on a CU, or their first waves on one SIMD, queue for; up to
+// kFusedHalvesCodes, where half a quarter a thread is at most one wave a SIMD,
+// the threads take 16 codes (1024 -> 6144 at M = 1 5.3 -> 4.7 us, 4096 -> 4096
+// 4.7 -> 4.45, 4096 -> 14336 7.1 -> 6.65; at 8192 codes 8192 -> 8192 8.4 -> 8.9).
 constexpr int kFusedMaxM = 8, kFusedQPT = 2;
 constexpr int64_t kFusedMaxCodes = 32768, kFusedMaxCodes5 = 24576, kFusedMaxCodes5Wide = 16384;
+constexpr int64_t kFusedHalvesCodes = 4096;
 constexpr int kDecodeWaves = 8;
-static_assert(kFusedMaxCodes <= (int64_t)kFusedQPT * 32 * 64 * kDecodeWaves, "every code has a thread");
+static_assert(kFusedHalvesCodes <= 16 * 64 * kDecodeWaves && kFusedMaxCodes <= (int64_t)kFusedQPT * 32 * 64 * kDecodeWaves,
+              "every code has a thread");
 
 // Items in flight per wave: stages of WM X fragments, WN B fragments and
 // their scales filling about 96 registers (measured: a deeper ring of the 64 x 64
@@ -989,7 +1000,7 @@ struct StreamDepth {
 // high plane and a folded 4-bit low plane (mq_quantize_act8); each product
 // takes the low-plane MFMA and the fp8 x fp6 MFMA of the high plane chained
 // on its result (both exact), the rest is unchanged.
-template <int WM, int WN, int WGM, int WGN, bool RAW, bool FQ, bool A8 = false, bool XS = false, bool PT = false>
+template <int WM, int WN, int WGM, int WGN, bool RAW, int FQ, bool A8 = false, bool XS = false, bool PT = false>
 __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs a) {
     static_assert(WN * WGN == 1 || WN * WGN == 2 || WN * WGN == 4 || WN * WGN == 8,
                   "tile columns inside one block row");
@@ -1284,19 +1295,20 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
         pin_all();
     };
 
-    // FQ, part 1: this thread's quarters of X (quarter t + 512 i of the rows in
-    // turn), loaded first so that they are the first loads to land
-    const int nq = K / 32;
-    Halves<32> xv[FQ ? kFusedQPT : 1];
-    int xm[FQ ? kFusedQPT : 1];
+    // FQ, part 1: this thread's pieces of X (FQ values each; piece t + 512 i of
+    // the rows in turn), loaded first so that they are the first loads to land
+    constexpr int kFC = FQ ? FQ : 32, kFP = FQ == 16 ? 1 : kFusedQPT;
+    const int npc = K / kFC;
+    Halves<kFC> xv[FQ ? kFP : 1];
+    int xm[FQ ? kFP : 1];
     if constexpr (FQ) {
         if (threadIdx.x < kFusedMaxM) amax_sh[threadIdx.x] = 0u;
 #pragma unroll
-        for (int i = 0; i < kFusedQPT; ++i) {
+        for (int i = 0; i < kFP; ++i) {
             const int idx = (int)threadIdx.x + i * 64 * NW;
-            xv[i] = Halves<32>{};
-            xm[i] = idx / nq;
-            if (idx < M * nq) xv[i] = load_halves<32>(a.X + (int64_t)xm[i] * a.ldx + 32 * (idx - xm[i] * nq));
+            xv[i] = Halves<kFC>{};
+            xm[i] = idx / npc;
+            if (idx < M * npc) xv[i] = load_halves<kFC>(a.X + (int64_t)xm[i] * a.ldx + kFC * (idx - xm[i] * npc));
         }
     }
 
@@ -1350,12 +1362,12 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
 
     if constexpr (FQ) {
         // FQ, part 2: row maxima across the workgroup (on the sign-cleared fp16
-        // bits; a wave whose quarters are all of one row reduces them first, so
+        // bits; a wave whose pieces are all of one row reduces them first, so
         // that the LDS atomics do not queue on one address), scales, codes
         __syncthreads();                                   // amax_sh cleared
 #pragma unroll
-        for (int i = 0; i < kFusedQPT; ++i) {
-            const uint32_t cm = absmax_bits(xv[i]);   // 0 past the last quarter
+        for (int i = 0; i < kFP; ++i) {
+            const uint32_t cm = absmax_bits(xv[i]);       // 0 past the last piece
             const int first = __builtin_amdgcn_readfirstlane(xm[i]), last = __builtin_amdgcn_readlane(xm[i], 63);
             if (first >= M) continue;
             if (first == last) {
@@ -1368,8 +1380,9 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
         __syncthreads();
         if ((int)threadIdx.x < M) sx_sh[threadIdx.x] = scale_bits_from_amax(half_bits_to_float((uint16_t)amax_sh[threadIdx.x]));
 #pragma unroll
-        for (int i = 0; i < kFusedQPT; ++i) {
-            const int m = xm[i], c = (int)threadIdx.x + i * 64 * NW - m * nq, g = c >> 2, j = c & 3;
+        for (int i = 0; i < kFP; ++i) {
+            const int m = xm[i], c = (int)threadIdx.x + i * 64 * NW - m * npc;
+            const int g = c / (kGroup / kFC), e0 = c % (kGroup / kFC) * kFC, j = e0 >> 5;   // codes e0 .. of group g, quarter j
             if (m < M) {
                 const uint32_t amax = amax_sh[m];
                 float s = half_bits_to_float(scale_bits_from_amax(half_bits_to_float((uint16_t)amax)));
@@ -1378,12 +1391,21 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
                     nonfinite_scale<false>(s, inv_s);
                     nonfinite_values<false>(xv[i], amax);
                 }
-                float q[32];
+                float q[kFC];
                 quant_codes(xv[i], s, inv_s, (float)kQmax, q);
                 const u32x6 d = operand_dwords(q);
-                *reinterpret_cast<uint4*>(&xs[xs_main(g, m, j)]) = make_uint4(d[0], d[1], d[2], d[3]);
-                *reinterpret_cast<uint2*>(&xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)m) * 32u +
-                                              (uint32_t)j * 8u]) = make_uint2(d[4], d[5]);
+                uint8_t* main = &xs[xs_main(g, m, j)];
+                uint8_t* tail = &xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)m) * 32u + (uint32_t)j * 8u];
+                if constexpr (FQ == 32) {
+                    *reinterpret_cast<uint4*>(main) = make_uint4(d[0], d[1], d[2], d[3]);
+                    *reinterpret_cast<uint2*>(tail) = make_uint2(d[4], d[5]);
+                } else if (e0 & 16) {                      // dwords 3 .. 5 of the quarter
+                    *reinterpret_cast<uint32_t*>(main + 12) = d[0];
+                    *reinterpret_cast<uint2*>(tail) = make_uint2(d[1], d[2]);
+                } else {
+                    *reinterpret_cast<uint2*>(main) = make_uint2(d[0], d[1]);
+                    *reinterpret_cast<uint32_t*>(main + 8) = d[2];
+                }
             }
         }
         __syncthreads();
@@ -1513,6 +1535,9 @@ static int decode_spw_one_row(int N) {
 // and 16 rows: 18.55 -> 18.25 and 20.2 -> 19.6 us).  Every wave needs a group
 // of each tile (K >= 8 x 128) and a workgroup at most 64 tiles (one a lane);
 // 0: one workgroup per tile.
+// (most_per_cu: the resident workgroups a CU that the grid counts on.  Fused
+// quantisation: two, also where the registers would let three in, since the
+// rounds of three were slower: 3072 -> 28672 at M = 1 11.0 -> 11.9 us.)
 // Resident workgroups per CU of a decode kernel with this much dynamic LDS
 // (the runtime's occupancy query, remembered per kernel and LDS size).
 static int decode_occupancy(const void* kernel, size_t lds_bytes) {
@@ -1537,21 +1562,21 @@ static int decode_occupancy(const void* kernel, size_t lds_bytes) {
     return occ;
 }
 
-static unsigned decode_grid(const void* kernel, size_t lds_bytes, int K, int64_t tiles) {
+static unsigned decode_grid(const void* kernel, size_t lds_bytes, int most_per_cu, int K, int64_t tiles) {
     if (tiles <= kCUs || K / kGroup < kDecodeWaves) return 0;     // one round whatever the occupancy
-    const int64_t slots = (int64_t)decode_occupancy(kernel, lds_bytes) * kCUs;
+    const int64_t slots = (int64_t)std::min(decode_occupancy(kernel, lds_bytes), most_per_cu) * kCUs;
     if (tiles <= slots) return 0;
     const int64_t per = (tiles + slots - 1) / slots;
     if (per > 64) return (unsigned)(((tiles + 63) / 64 + 7) / 8 * 8);
     return (unsigned)slots;
 }
 
-template <int WM, int WN, int WGM, int WGN, bool RAW, bool FQ, bool A8 = false, bool XS = false>
+template <int WM, int WN, int WGM, int WGN, bool RAW, int FQ, bool A8 = false, bool XS = false>
 static void launch_stream(const GemmArgs& a, size_t xs_bytes, hipStream_t stream) {
     const int64_t tiles = (int64_t)((a.M + 16 * WM * WGM - 1) / (16 * WM * WGM)) * (a.N / (16 * WN * WGN));
     if constexpr (FQ || XS) {
         const auto pt = gemm_stream_kernel<WM, WN, WGM, WGN, RAW, FQ, A8, XS, true>;
-        const unsigned grid = decode_grid(reinterpret_cast<const void*>(pt), xs_bytes, a.K, tiles);
+        const unsigned grid = decode_grid(reinterpret_cast<const void*>(pt), xs_bytes, FQ ? 2 : 8, a.K, tiles);
         if (grid > 0) {
             hipLaunchKernelGGL(pt, dim3(grid), dim3(64 * kDecodeWaves), xs_bytes, stream, a);
             return;
@@ -1572,8 +1597,8 @@ void launch_medium_tiles(const GemmArgs& a, bool tile64, hipStream_t stream);
 #ifdef MQ_MEDIUM_TU
 template <bool RAW>
 void launch_medium_tiles(const GemmArgs& a, bool tile64, hipStream_t stream) {
-    if (tile64) launch_stream<4, 4, 1, 1, RAW, false>(a, 0, stream);
-    else launch_stream<2, 4, 1, 1, RAW, false>(a, 0, stream);
+    if (tile64) launch_stream<4, 4, 1, 1, RAW, 0>(a, 0, stream);
+    else launch_stream<2, 4, 1, 1, RAW, 0>(a, 0, stream);
 }
 template void launch_medium_tiles<false>(const GemmArgs&, bool, hipStream_t);
 template void launch_medium_tiles<true>(const GemmArgs&, bool, hipStream_t);
@@ -1590,17 +1615,17 @@ static size_t staged_act_bytes(const GemmArgs& a, int wm, int spw) {
     return (xb <= kStageMaxBytes && xb + red <= kDecodeLdsBytes) ? xb : 0;
 }
 
-template <int WM, int SPW, bool RAW, bool FQ>
+template <int WM, int SPW, bool RAW, int FQ>
 static void launch_decode_spw(const GemmArgs& a, size_t xs_bytes, hipStream_t stream) {
     if constexpr (!FQ) {
         const size_t xb = staged_act_bytes(a, WM, SPW);
-        if (xb > 0) return launch_stream<WM, SPW, 1, 1, RAW, false, false, true>(a, xb, stream);
+        if (xb > 0) return launch_stream<WM, SPW, 1, 1, RAW, 0, false, true>(a, xb, stream);
     }
     launch_stream<WM, SPW, 1, 1, RAW, FQ>(a, xs_bytes, stream);
 }
 
 // xs_bytes: LDS for the quantised rows (fused quantisation), 0 otherwise
-template <int WM, bool RAW, bool FQ>
+template <int WM, bool RAW, int FQ>
 static void launch_decode(const GemmArgs& a, int spw, size_t xs_bytes, hipStream_t stream) {
     if (spw >= 2) return launch_decode_spw<WM, 2, RAW, FQ>(a, xs_bytes, stream);
     launch_decode_spw<WM, 1, RAW, FQ>(a, xs_bytes, stream);
@@ -1760,8 +1785,8 @@ static mq_status launch(mq_variant variant, const GemmArgs& args, void* workspac
             hipLaunchKernelGGL((gemm_tiled_kernel<8, 4, RAW, false, false, true>), dim3((unsigned)tiles),
                                dim3(TS::kThreads), 0, stream, a, 0, (float*)nullptr);
     } else if (variant == MQ_VARIANT_SKINNY) {
-        if (a.M <= 16) launch_decode<1, RAW, false>(a, a.M == 1 ? decode_spw_one_row(a.N) : decode_spw(a.N), 0, stream);
-        else launch_decode<2, RAW, false>(a, decode_spw(a.N), 0, stream);
+        if (a.M <= 16) launch_decode<1, RAW, 0>(a, a.M == 1 ? decode_spw_one_row(a.N) : decode_spw(a.N), 0, stream);
+        else launch_decode<2, RAW, 0>(a, decode_spw(a.N), 0, stream);
     } else {
         const int64_t tiles = (int64_t)((a.M + kTB - 1) / kTB) * (a.N / kTB);
         if (tiles > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
@@ -1910,11 +1935,11 @@ static mq_status launch_a8(GemmArgs a, hipStream_t stream) {
     if (rs != MQ_OK) return rs;
     if (a.M <= 16) {
         const int spw = decode_spw(a.N);
-        if (spw == 2) launch_stream<1, 2, 1, 1, RAW, false, true>(a, 0, stream);
-        else launch_stream<1, 1, 1, 1, RAW, false, true>(a, 0, stream);
+        if (spw == 2) launch_stream<1, 2, 1, 1, RAW, 0, true>(a, 0, stream);
+        else launch_stream<1, 1, 1, 1, RAW, 0, true>(a, 0, stream);
     } else if (a.M <= 32) {
-        if (decode_spw(a.N) >= 2) launch_stream<2, 2, 1, 1, RAW, false, true>(a, 0, stream);
-        else launch_stream<2, 1, 1, 1, RAW, false, true>(a, 0, stream);
+        if (decode_spw(a.N) >= 2) launch_stream<2, 2, 1, 1, RAW, 0, true>(a, 0, stream);
+        else launch_stream<2, 1, 1, 1, RAW, 0, true>(a, 0, stream);
     } else {
         using TS = TileShape<4, 4>;
         const int64_t tiles = (int64_t)((a.M + TS::kTM - 1) / TS::kTM) * (a.N / TS::kTN);
@@ -1929,8 +1954,8 @@ static mq_status launch_a8(GemmArgs a, hipStream_t stream) {
         const int64_t t64 = (int64_t)((a.M + 63) / 64) * (a.N / 64);
         const int64_t t32 = (int64_t)((a.M + 31) / 32) * (a.N / 64);
         if (t32 > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
-        if (t64 >= kCUs) launch_stream<4, 4, 1, 1, RAW, false, true>(a, 0, stream);
-        else launch_stream<2, 4, 1, 1, RAW, false, true>(a, 0, stream);
+        if (t64 >= kCUs) launch_stream<4, 4, 1, 1, RAW, 0, true>(a, 0, stream);
+        else launch_stream<2, 4, 1, 1, RAW, 0, true>(a, 0, stream);
     }
     return mq_host::launch_status();
 }
@@ -2014,7 +2039,9 @@ static mq_status linear_impl(int M, int N, int K, const void* X, int ldx,
         if (st != MQ_OK) return st;
         // (at four rows two strips measured faster than one on the wide
         // layers, where one row takes one: 5120 -> 25600 19.9 -> 19.1 us)
-        launch_decode<1, false, true>(a, M == 1 ? decode_spw_one_row(N) : decode_spw(N), (size_t)M * (K / 4) * 3, stream);
+        const int spw = M == 1 ? decode_spw_one_row(N) : decode_spw(N);
+        if ((int64_t)M * K <= kFusedHalvesCodes) launch_decode<1, false, 16>(a, spw, (size_t)M * (K / 4) * 3, stream);
+        else launch_decode<1, false, 32>(a, spw, (size_t)M * (K / 4) * 3, stream);
         return mq_host::launch_status();
     }
     // quantise into the workspace, then the fused GEMM
