@@ -146,6 +146,15 @@ size_t mq_fused_gemm_workspace_size(int M, int N, int K);
 mq_status mq_fused_gemm_plan(int M, int N, int K, int* variant, int* splits);
 
 /*
+ * Output tile (rows x columns of Y) of one workgroup of that launch, for AUTO
+ * or an explicit variant (one that does not apply to the shape is replaced as
+ * in mq_fused_gemm_variant); host logic, errors as mq_fused_gemm_plan.  A last
+ * tile row may be lower.  The decode kernels' tiles are 16 or 32 rows however
+ * few M is.
+ */
+mq_status mq_fused_gemm_tile(mq_variant variant, int M, int N, int K, int* rows, int* cols);
+
+/*
  * Fused dense + sparse-residual W4A4 GEMM (Section 3 Eq. (4) with Eq. (2)'s
  * scale factorisation per group; Section 4.2 "Kernel Fusion" and
  * "Overlapped pipeline"):
@@ -257,6 +266,12 @@ mq_status mq_fused_gemm_a8(int M, int N, int K,
                            const int32_t* res_rowptr, const int32_t* res_kb, int nnzb,
                            const uint8_t* Rq, const void* s_r,
                            void* Y, int ldy, hipStream_t stream);
+
+/*
+ * Output tile of one workgroup of the W4A8 launch (as mq_fused_gemm_tile):
+ * 128 x 256 where the tiled kernel takes it.
+ */
+mq_status mq_fused_gemm_a8_tile(int M, int N, int K, int* rows, int* cols);
 
 /* Raw integer sums of the W4A8 layer (testing): Tb, Tr int32 [M, N];
  * |Tb|, |Tr| <= 889 K < 2^31. */

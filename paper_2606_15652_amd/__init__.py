@@ -30,6 +30,8 @@ _SIG = {
     "mq_quantize_act": (_I, [_P, _I, _I, _I, _P, _P, _P]),
     "mq_fused_gemm_workspace_size": (C.c_size_t, [_I, _I, _I]),
     "mq_fused_gemm_plan": (_I, [_I, _I, _I, _P, _P]),
+    "mq_fused_gemm_tile": (_I, [_I, _I, _I, _I, _P, _P]),
+    "mq_fused_gemm_a8_tile": (_I, [_I, _I, _I, _P, _P]),
     "mq_fused_gemm": (_I, [_I, _I, _I, _P, _P, _P, _P, _P, _P, _I, _P, _P, _P, _I, _P,
                           C.c_size_t, _P]),
     "mq_linear_workspace_size": (C.c_size_t, [_I, _I, _I]),
@@ -218,6 +220,21 @@ def plan(M: int, N: int, K: int):
     _check("mq_fused_gemm_plan", load().mq_fused_gemm_plan(M, N, K, C.byref(v), C.byref(sp)))
     name = {code: n for n, code in VARIANTS.items()}[v.value]
     return name, sp.value
+
+
+def tile(M: int, N: int, K: int, variant: str = "auto"):
+    """(rows, columns) of the output tile one workgroup of that launch takes
+    (host logic only)."""
+    r, c = C.c_int(0), C.c_int(0)
+    _check("mq_fused_gemm_tile", load().mq_fused_gemm_tile(VARIANTS[variant], M, N, K, C.byref(r), C.byref(c)))
+    return r.value, c.value
+
+
+def a8_tile(M: int, N: int, K: int):
+    """(rows, columns) of the output tile of the W4A8 launch (host logic only)."""
+    r, c = C.c_int(0), C.c_int(0)
+    _check("mq_fused_gemm_a8_tile", load().mq_fused_gemm_a8_tile(M, N, K, C.byref(r), C.byref(c)))
+    return r.value, c.value
 
 
 def fused_gemm(Xq, s_x, pw: PackedWeight, out=None, variant: str = "auto", stream=None,

@@ -1717,6 +1717,12 @@ static bool medium_preferred(int M, int N, int K) {
     return t128 < kMediumTargetWGs && 2 * t64 <= half_rounds * kCUs;
 }
 
+// Rows of the 64-column streaming tiles: one workgroup per CU (its ring takes
+// most of the LDS), 64 rows when those tiles alone give every CU one, else 32.
+static int medium_tile_rows(int M, int N) {
+    return (int64_t)((M + 63) / 64) * (N / 64) >= kCUs ? 64 : 32;
+}
+
 // Byte sizes of the operands and buffer resources spanning each of them.
 // Whole-operand resources take 32-bit offsets (and offsets from 2 GB up serve
 // as "past the end"), so every operand must stay below 2 GB.
@@ -1766,12 +1772,8 @@ static mq_status launch(mq_variant variant, const GemmArgs& args, void* workspac
     a.y16 = (!RAW && a.Y && mq_host::aligned(a.Y, 16)) ? 1 : 0;
     variant = resolve_variant(variant, a.M, a.N, a.K);
     if (variant == MQ_VARIANT_MEDIUM) {
-        // one workgroup per CU (its ring takes most of the LDS): 64-row tiles
-        // when they alone give every CU one, else 32-row ones
-        const int64_t t64 = (int64_t)((a.M + 63) / 64) * (a.N / 64);
-        const int64_t t32 = (int64_t)((a.M + 31) / 32) * (a.N / 64);
-        if (t32 > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
-        launch_medium_tiles<RAW>(a, t64 >= kCUs, stream);
+        if ((int64_t)((a.M + 31) / 32) * (a.N / 64) > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
+        launch_medium_tiles<RAW>(a, medium_tile_rows(a.M, a.N) == 64, stream);
     } else if (variant == MQ_VARIANT_TILED_LARGE) {
         using TS = TileShape<8, 4>;
         a.tile_rows = large_tile_rows(a.M, a.N);
@@ -1857,6 +1859,29 @@ extern "C" mq_status mq_fused_gemm_plan(int M, int N, int K, int* variant, int* 
     return MQ_OK;
 }
 
+extern "C" mq_status mq_fused_gemm_tile(mq_variant variant, int M, int N, int K, int* rows, int* cols) {
+    if (!rows || !cols || M < 1 || M > (1 << 24) || variant < MQ_VARIANT_AUTO || variant > MQ_VARIANT_MEDIUM)
+        return MQ_ERR_INVALID_ARG;
+    if (!mq_host::shape_ok(N, K)) return MQ_ERR_UNSUPPORTED_SHAPE;
+    switch (resolve_variant(variant, M, N, K)) {
+        case MQ_VARIANT_SKINNY:
+            *rows = M <= 16 ? 16 : 32;
+            *cols = 16 * (M == 1 ? decode_spw_one_row(N) : decode_spw(N));
+            break;
+        case MQ_VARIANT_MEDIUM:
+            *rows = medium_tile_rows(M, N);
+            *cols = 64;
+            break;
+        case MQ_VARIANT_TILED_LARGE:
+            *rows = large_tile_rows(M, N);
+            *cols = 256;
+            break;
+        default:
+            *rows = *cols = kTB;
+    }
+    return MQ_OK;
+}
+
 extern "C" mq_status mq_fused_gemm_variant(mq_variant variant, int M, int N, int K,
                                            const uint8_t* Xq, const void* s_x,
                                            const uint8_t* Wq, const void* s_w,
@@ -1917,16 +1942,26 @@ extern "C" mq_status mq_fused_gemm_acc_i32(mq_variant variant, int M, int N, int
 // streaming tiles (32 x 64 when those are fewer than the CUs).
 // ---------------------------------------------------------------------------
 // The tiled kernel takes a W4A8 layer when its 128 x 256 tiles need at most a
-// third of the rounds of the 64 x 64 streaming tiles (one workgroup a CU in
-// both): a tiled round measured 2.7 to 2.9 streaming ones (K = 4096: 47 against
-// 16 to 17 us; K = 14336: 143 against 47 to 50).  Three rounds against one:
-// 5120 -> 5120 at M = 512 57.0 us tiled, 61.6 streamed; four: 4096 -> 4096 at
-// M = 1024 47.6 and 68.0, 8192 -> 28672 at M = 128 92 and 116; two: 4096 -> 4096
-// at M = 512 47 and 37, 8192 -> 28672 at M = 64 91 and 63.
-static bool a8_tiled_preferred(int M, int N) {
+// quarter of the rounds of the 64 x 64 streaming tiles (one workgroup a CU in
+// both), or a third where K is short: a
+// tiled round measured 2.7 to 2.9 streaming ones (K = 4096: 47 against 16 to 17
+// us; K = 14336: 143 against 47 to 50), but the streaming tiles' last round costs
+// less when it is short, and skewed residual blocks cost a tiled round up to a
+// quarter more.  Four rounds: 4096 -> 4096 at M = 1024 47.5 us tiled, 67.9
+// streamed; 14336 -> 5120 at M = 577 142 and 187; the least 14336 -> 14336 at
+// M = 256, 143 and 184, skewed 184 and 178.  Three, up to K = 4096: 1024 -> 8192 at
+// M = 384 19.0 and 21.9, 4096 -> 8192 at M = 384 47.5 and 52.6, skewed 59.0 and 63.9 (but
+// at M = 300 47.5 and 50.1, skewed 59.0 and 55.2), and up to 6144 where the third is at
+// least half full (5120 -> 4096 at M = 640 56.8 and 62.2; 5120 -> 5120 at M = 400, 2.2
+// rounds, 56 and 53).  Not at longer K (8192 -> 8192 at M = 300 skewed 107 and 94,
+// 28672 -> 5120 at M = 400 272 and 232) nor on one row of tiles (4096 -> 24576 at
+// M = 128 50.9 and 53.3, skewed 62.8 and 59.2).  Two: 4096 -> 4096 at M = 512 47 and
+// 37, 8192 -> 28672 at M = 64 91 and 63.
+static bool a8_tiled_preferred(int M, int N, int K) {
     if (N % TileShape<4, 4>::kTN != 0) return false;
     const int64_t tt = (int64_t)((M + 127) / 128) * (N / 256), ts = (int64_t)((M + 63) / 64) * (N / 64);
-    return (ts + kCUs - 1) / kCUs >= 3 * ((tt + kCUs - 1) / kCUs);
+    const int64_t rt = (tt + kCUs - 1) / kCUs, rs = (ts + kCUs - 1) / kCUs;
+    return rs >= 4 * rt || (rs >= 3 * rt && M > 128 && (K <= 4096 || (K <= 6144 && 2 * ts >= 5 * kCUs * rt)));
 }
 
 template <bool RAW>
@@ -1943,7 +1978,7 @@ static mq_status launch_a8(GemmArgs a, hipStream_t stream) {
     } else {
         using TS = TileShape<4, 4>;
         const int64_t tiles = (int64_t)((a.M + TS::kTM - 1) / TS::kTM) * (a.N / TS::kTN);
-        if (a8_tiled_preferred(a.M, a.N)) {
+        if (a8_tiled_preferred(a.M, a.N, a.K)) {
             if (tiles > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
             a.y16 = (!RAW && a.Y && mq_host::aligned(a.Y, 16)) ? 1 : 0;
             a.rank_rows = tiles <= kCUs;
@@ -1951,13 +1986,27 @@ static mq_status launch_a8(GemmArgs a, hipStream_t stream) {
                                stream, a, 0, (float*)nullptr);
             return mq_host::launch_status();
         }
-        const int64_t t64 = (int64_t)((a.M + 63) / 64) * (a.N / 64);
-        const int64_t t32 = (int64_t)((a.M + 31) / 32) * (a.N / 64);
-        if (t32 > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
-        if (t64 >= kCUs) launch_stream<4, 4, 1, 1, RAW, 0, true>(a, 0, stream);
+        if ((int64_t)((a.M + 31) / 32) * (a.N / 64) > 0x7fffffff) return MQ_ERR_UNSUPPORTED_SHAPE;
+        if (medium_tile_rows(a.M, a.N) == 64) launch_stream<4, 4, 1, 1, RAW, 0, true>(a, 0, stream);
         else launch_stream<2, 4, 1, 1, RAW, 0, true>(a, 0, stream);
     }
     return mq_host::launch_status();
+}
+
+extern "C" mq_status mq_fused_gemm_a8_tile(int M, int N, int K, int* rows, int* cols) {
+    if (!rows || !cols || M < 1 || M > (1 << 24)) return MQ_ERR_INVALID_ARG;
+    if (!mq_host::shape_ok(N, K)) return MQ_ERR_UNSUPPORTED_SHAPE;
+    if (M <= 32) {
+        *rows = M <= 16 ? 16 : 32;
+        *cols = 16 * decode_spw(N);
+    } else if (a8_tiled_preferred(M, N, K)) {
+        *rows = TileShape<4, 4>::kTM;
+        *cols = TileShape<4, 4>::kTN;
+    } else {
+        *rows = medium_tile_rows(M, N);
+        *cols = 64;
+    }
+    return MQ_OK;
 }
 
 extern "C" mq_status mq_fused_gemm_a8(int M, int N, int K,

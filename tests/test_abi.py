@@ -210,3 +210,34 @@ def test_auto_plan_validation(lib):
     assert lib.mq_fused_gemm_plan(16, 4000, 4096, C.byref(v), C.byref(s)) == SHAPE
     assert lib.mq_fused_gemm_plan(16, 4096, 100, C.byref(v), C.byref(s)) == SHAPE
 
+
+
+# (M, N, K): the W4A8 launch's tile -- tiled from four streaming rounds for one,
+# three at short K and more than one row of tiles; never beside a remainder of N
+A8_TILES = [
+    ((1, 4096, 4096), (16, 16)), ((32, 8192, 4096), (32, 32)), ((33, 4096, 4096), (32, 64)), ((256, 4096, 4096), (64, 64)),
+    ((512, 4096, 4096), (64, 64)),                                     # two rounds
+    ((768, 4096, 4096), (128, 256)), ((768, 4096, 14336), (64, 64)),   # three
+    ((400, 5120, 4096), (128, 256)), ((400, 5120, 5120), (64, 64)), ((512, 5120, 6144), (128, 256)),
+    ((512, 5120, 8192), (64, 64)), ((400, 5120, 28672), (64, 64)), ((300, 8192, 8192), (64, 64)),
+    ((128, 24576, 4096), (64, 64)), ((129, 24576, 4096), (128, 256)),  # one row of tiles, two
+    ((577, 5120, 14336), (128, 256)), ((1024, 4096, 28672), (128, 256)), ((128, 28672, 8192), (128, 256)),
+    ((2048, 14336, 4096), (128, 256)), ((2048, 1152, 1024), (64, 64)), ((2048, 1152, 4096), (64, 64)),
+]
+
+
+@pytest.mark.parametrize("shape,expect", A8_TILES, ids=[f"M{m}_N{n}_K{k}" for (m, n, k), _ in A8_TILES])
+def test_a8_tile(lib, shape, expect):
+    import paper_2606_15652_amd as mq
+    assert mq.a8_tile(*shape) == expect
+
+
+def test_tile_validation(lib):
+    import ctypes as C
+    r, c = C.c_int(0), C.c_int(0)
+    for f in (lambda *a: lib.mq_fused_gemm_tile(0, *a), lib.mq_fused_gemm_a8_tile):
+        assert f(0, 4096, 4096, C.byref(r), C.byref(c)) == INVALID
+        assert f(16, 4096, 4096, None, C.byref(c)) == INVALID
+        assert f(16, 4000, 4096, C.byref(r), C.byref(c)) == SHAPE
+        assert f(16, 4096, 100, C.byref(r), C.byref(c)) == SHAPE
+    assert lib.mq_fused_gemm_tile(5, 16, 4096, 4096, C.byref(r), C.byref(c)) == INVALID

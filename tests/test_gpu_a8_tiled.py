@@ -18,6 +18,7 @@ CASES = [(1157, 2048, 384, 9, 0), (2049, 1024, 128, 3, 0), (700, 3328, 256, 0, 0
 
 @pytest.mark.parametrize("M,N,K,nnzb,off", CASES)
 def test_a8_tiled_parity(tc, mq, orc, M, N, K, nnzb, off):
+    assert mq.a8_tile(M, N, K) == (128, 256)
     _, s_x, Wq, s_w, rowptr, kb, sel, Rq, s_r = random_operands(M, N, K, nnzb, seed=M + N + K)
     codes = np.random.default_rng(M * 3 + N).integers(-127, 128, (M, K)).astype(np.int8)
     Tb_ref, Tr_ref, Y64 = orc.linear_a8(codes, s_x, orc_pw(orc, N, K, Wq, s_w, rowptr, kb, sel, Rq, s_r))
