@@ -724,14 +724,18 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             }
         };
         // The activation operand is read two rows ahead (one row of MFMAs
-        // and epilogue does not cover the LDS latency).
+        // and epilogue does not cover the LDS latency).  The raw sums of the
+        // 256-row tile, twice the accumulators, spill, and one operand less
+        // in flight is faster (K = N = M = 4096 162 -> 136 us): one row.
+        constexpr bool kNear = RAW && WM == 8;
         AOp av = a_row(std::integral_constant<int, 0>{});
         AOp an = av;
-        if constexpr (NR > 1) an = a_row(std::integral_constant<int, 1>{});
+        if constexpr (NR > 1 && !kNear) an = a_row(std::integral_constant<int, 1>{});
         static_for<NR>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
+            if constexpr (kNear && i + 1 < NR) an = a_row(std::integral_constant<int, i + 1>{});
             AOp ann = an;
-            if constexpr (i + 2 < NR) ann = a_row(std::integral_constant<int, i + 2>{});
+            if constexpr (!kNear && i + 2 < NR) ann = a_row(std::integral_constant<int, i + 2>{});
             if constexpr (A8) {
                 // low-plane MFMAs, half of the row before's epilogue, high-plane
                 // MFMAs, the other half (the scheduling barriers hold this order:
