@@ -429,11 +429,13 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
             const cint32_t* rowptr = (const cint32_t*)(a.rowptr);
             rp[b] = rowptr[br[b]];
             re[b] = rowptr[br[b] + 1];
-            while (rp[b] < re[b] && res_kb[rp[b]] < gb) ++rp[b];
-            if constexpr (SPLIT) {                         // the entries of this split only
-                int e = rp[b];
-                while (e < re[b] && res_kb[e] < ge) ++e;
-                re[b] = e;
+            if constexpr (SPLIT) {                         // columns ascend: the first entry at or after gb
+                int hi = re[b];
+                while (rp[b] < hi) {
+                    const int mid = (rp[b] + hi) >> 1;
+                    if (res_kb[mid] < gb) rp[b] = mid + 1;
+                    else hi = mid;
+                }
             }
             if (rp[b] < re[b]) nk[b] = res_kb[rp[b]];
         }
@@ -517,12 +519,12 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
         wso += (uint32_t)N * kRow;
         sso += (uint32_t)N * 2u;
     };
-    // block row b's residual block at group g (-1: none); groups are asked for in order
+    // block row b's residual block at group g (-1: none, and from ge on); groups are asked for in order
     auto next_blocks = [&](int g, int (&p)[NBR]) {
 #pragma unroll
         for (int b = 0; b < NBR; ++b) {
             p[b] = -1;
-            if (nk[b] == g) {
+            if (nk[b] == g && (!SPLIT || g < ge)) {
                 p[b] = rp[b]++;
                 nk[b] = rp[b] < re[b] ? res_kb[rp[b]] : 0x7fffffff;
             }
