@@ -63,8 +63,9 @@
  *   layout above.
  * - Inputs must be finite.  Outputs must not alias inputs.
  * - Thread safety: every call may be made concurrently from several host
- *   threads.  The only global state is the per-device address of the
- *   scratch array of mq_linear_noalloc, set once per device under a lock.
+ *   threads.  The only global state, both under locks, is the per-device
+ *   address of the scratch array of mq_linear_noalloc, set once per device, and
+ *   a fixed-size table of how many workgroups of a decode kernel fit on a CU.
  */
 #ifndef MQ_H
 #define MQ_H

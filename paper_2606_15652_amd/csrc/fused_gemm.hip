@@ -29,6 +29,7 @@
 //    columns.  Medium M: 64 x 64 (or 32 x 64) tiles, each wave the whole tile
 //    over an eighth of K, so every operand piece is read once per workgroup.
 #include "mq_device.h"
+#include "residency.h"
 
 #include <stddef.h>
 
@@ -1544,28 +1545,20 @@ static int decode_spw_one_row(int N) {
 // (most_per_cu: the resident workgroups a CU that the grid counts on.  Fused
 // quantisation: two, also where the registers would let three in, since the
 // rounds of three were slower: 3072 -> 28672 at M = 1 11.0 -> 11.9 us.)
-// Resident workgroups per CU of a decode kernel with this much dynamic LDS
-// (the runtime's occupancy query, remembered per kernel and LDS size).
+// Resident workgroups per CU of a decode kernel with this much dynamic LDS (the
+// runtime's occupancy query; the same on every device, the code is gfx950's only).
 static int decode_occupancy(const void* kernel, size_t lds_bytes) {
-    struct Entry {
-        const void* kernel;
-        size_t lds;
-        int occ;
-    };
     static std::mutex mutex;
-    static Entry cache[64];
-    static int used = 0;
+    static mq_host::ResidencyTable table;
     std::lock_guard<std::mutex> lock(mutex);
-    for (int i = 0; i < used; ++i)
-        if (cache[i].kernel == kernel && cache[i].lds == lds_bytes) return cache[i].occ;
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, 64 * kDecodeWaves, lds_bytes) != hipSuccess) {
-        (void)hipGetLastError();    // a failed query must not surface as the launch's error
-        return 1;
-    }
-    if (occ < 1) occ = 1;
-    if (used < 64) cache[used++] = Entry{kernel, lds_bytes, occ};
-    return occ;
+    return table.get(kernel, lds_bytes, [&] {
+        int occ = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, 64 * kDecodeWaves, lds_bytes) != hipSuccess) {
+            (void)hipGetLastError();    // a failed query must not surface as the launch's error
+            return 0;
+        }
+        return occ < 1 ? 1 : occ;
+    });
 }
 
 static unsigned decode_grid(const void* kernel, size_t lds_bytes, int most_per_cu, int K, int64_t tiles) {
