@@ -1647,15 +1647,20 @@ static void launch_decode(const GemmArgs& a, int spw, size_t xs_bytes, hipStream
 constexpr int kSmallRoundPct = 68;
 
 // Time of a tile of the large kernel with this many rows, in per cent of a
-// 256-row one (K = 4096: rounds of 42.6, 38.7 and 30.0 us with 256, 192 and 128
-// rows; below 128 the group's latencies are what is left).
+// 256-row one (rounds of 145 and 125 us with 256 and 192 rows over three rounds
+// at K = 14336, 42.6 and 30.0 us with 256 and 128 at K = 4096; below 128 rows the
+// group's latencies are what is left).
 static int tile_height_pct(int rows) {
     return rows > 192 ? 100 : rows > 128 ? 88 : 70;
 }
 
 // Estimated time of the large kernel on tiles of th rows, in the same units:
 // whole rounds of full tiles, then the last round, in which the CUs without a
-// full tile take the short tiles of the last tile row in turn.
+// full tile take the short tiles of the last tile row in turn; those still
+// left when the full tiles end follow them.  (14336 -> 14848 at M = 3392, 242 full
+// and 58 short tiles in the last round: 370 by this, 545 us; 1024 -> 26624 at
+// M = 1793: 71 us, 75.5 on the 192-row tiles that counting the left ones behind the
+// CUs' second short tile would choose.)
 static int64_t large_time_pct(int M, int N, int th) {
     const int64_t tn = N / 256, full = (M / th) * tn, last = M % th ? tn : 0, rem = full % kCUs;
     const int c = tile_height_pct(th), ct = tile_height_pct(M % th);
@@ -1664,10 +1669,7 @@ static int64_t large_time_pct(int M, int N, int th) {
         left -= kCUs - rem;
         t += ct;
     }
-    while (left > 0) {
-        left -= kCUs;
-        t = (t > c ? t : c) + ct;
-    }
+    for (int64_t end = c + ct; left > 0; left -= kCUs, end += ct) t = std::max(t, end);   // behind the full tiles
     return full / kCUs * c + (rem > 0 && t < c ? c : t);
 }
 

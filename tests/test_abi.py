@@ -232,6 +232,33 @@ def test_a8_tile(lib, shape, expect):
     assert mq.a8_tile(*shape) == expect
 
 
+# (M, N): rows of the large kernel's tiles
+TILE_ROWS = [
+    ((4096, 4096), 256), ((8192, 28672), 256), ((1157, 14336), 256),
+    ((2048, 5120), 192),                       # 220 tiles of 192 rows in one round, 160 of 256
+    ((4224, 8192), 192), ((2049, 16384), 192), ((2113, 16384), 192),   # 256 rows: two full rounds and one of short tiles
+    # 256 rows: the short tiles start on the CUs that the last round's full tiles leave
+    ((3392, 14848), 256), ((2561, 18944), 256), ((1793, 26624), 256), ((1601, 30464), 256), ((6977, 7168), 256),
+    ((1280, 14336), 192), ((700, 14336), 192), ((257, 1024), 128), ((449, 24576), 256),
+]
+
+
+@pytest.mark.parametrize("shape,rows", TILE_ROWS, ids=[f"M{m}_N{n}" for (m, n), _ in TILE_ROWS])
+def test_large_tile_rows(lib, shape, rows):
+    import paper_2606_15652_amd as mq
+    M, N = shape
+    assert mq.tile(M, N, 4096, "tiled_large") == (rows, 256)
+
+
+def test_tiles_of_the_plan(lib):
+    import paper_2606_15652_amd as mq
+    assert mq.tile(1, 4096, 4096) == (16, 16) and mq.tile(17, 8192, 4096) == (32, 32)
+    assert mq.tile(1, 14336, 4096) == (16, 32) and mq.tile(1, 28672, 4096) == (16, 16)
+    assert mq.tile(256, 4096, 4096) == (64, 64) and mq.tile(255, 1024, 4096) == (32, 64)
+    assert mq.tile(1536, 4096, 4096) == (128, 128) and mq.tile(512, 384, 4096, "tiled_large") == (128, 128)
+    assert mq.plan(513, 24576, 4096) == ("tiled", 1) and mq.plan(1153, 32000, 4096) == ("tiled_large", 1)
+
+
 def test_tile_validation(lib):
     import ctypes as C
     r, c = C.c_int(0), C.c_int(0)
