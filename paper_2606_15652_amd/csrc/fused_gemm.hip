@@ -77,44 +77,6 @@ __device__ __forceinline__ void pin(T& v) {
     asm volatile("" : "+v"(v));
 }
 
-// One m sub-tile row of one group: base MFMA + epilogue for each of the WN
-// column sub-tiles, then (HAS_RES) the residual MFMA + epilogue.  sw / sr carry
-// the scales times kCodeScale.  The caller picks HAS_RES once per group, so
-// this is straight-line code and every MFMA result is consumed inside the
-// basic block that produced it (the compiler's MFMA-to-VALU wait states are
-// only placed reliably within a block).  Raw mode adds the exact integer group
-// sums instead.
-template <int WN, bool RAW, bool HAS_RES>
-__device__ __forceinline__ void group_row(const i32x8 a, const i32x8 (&w)[WN], const i32x8 (&rr)[WN],
-                                          const float (&sw)[WN], const float (&sr)[WN],
-                                          f32x4 (&acc)[WN], i32x4 (&iacc)[WN], i32x4 (&racc)[WN]) {
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-        const f32x4 t = mfma_codes(a, w[j], zero);
-        if constexpr (RAW) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) iacc[j][r] += (int)(t[r] * kCodeScale);   // exact integer
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[j][r] = __builtin_fmaf(sw[j], t[r], acc[j][r]);
-        }
-    }
-    if constexpr (HAS_RES) {
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            const f32x4 t = mfma_codes(a, rr[j], zero);
-            if constexpr (RAW) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) racc[j][r] += (int)(t[r] * kCodeScale);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[j][r] = __builtin_fmaf(sr[j], t[r], acc[j][r]);
-            }
-        }
-    }
-}
-
 // --------------------------------------------------------------------------
 // Tiled kernel
 // --------------------------------------------------------------------------
@@ -153,8 +115,6 @@ __device__ __forceinline__ void group_row(const i32x8 a, const i32x8 (&w)[WN], c
 constexpr int kTB = 128;
 constexpr int kRankMaxNB = 512;     // block rows the tiled kernel ranks by residual count
 constexpr uint32_t kPastEnd = 0x80000000u;   // buffer offset past every operand (< 2 GB): reads zero
-
-__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 3); }
 
 // Tile order: blocks are dealt to the 8 XCDs round-robin, so give each XCD a
 // contiguous range of a grouped tile order (the CUs of one XCD then share
@@ -455,7 +415,7 @@ void gemm_tiled_kernel(GemmArgs a, int groups_per_split, float* __restrict__ par
     // share: loaders ld < NBR the weight scales of block row ld, loaders
     // NBR .. 2 NBR - 1 the residual scales of block row ld - NBR (256 B each).
     // Lane l takes row 16 b + l / 4 and physical chunk l % 4, i.e. logical
-    // chunk (l % 4) ^ swz(row) of that row, so each load instruction reads
+    // chunk (l % 4) ^ ((row / 2) % 4) of that row, so each load instruction reads
     // 1 KB of whole 64-byte rows, contiguous.
     // (A8: low-plane blocks 2 ld, 2 ld + 1 and the high-plane blocks 4 ld .. + 3,
     // eight rows of 128 bytes each: lane l takes row 8 b + l / 8 and physical

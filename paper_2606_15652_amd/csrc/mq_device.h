@@ -44,20 +44,15 @@ __device__ __forceinline__ uint16_t scale_bits_from_amax(float amax, int qmax = 
 // is exact (an fma: for q != 0 both terms are multiples of half an ulp of s
 // and |e| is at most about s; for q = 0, e = x); comparing |e| with s/2
 // (exact) moves q to the nearest integer, ties to the even one.
-// (The argument does not depend on the size of q: it holds for the INT8
-// activation codes of the W4A8 variant, qmax = 127, as well.)
-__device__ __forceinline__ int quant_code_max(float x, float s, float inv_s, int qmax) {
+__device__ __forceinline__ int quant_code(float x, float s, float inv_s) {
     float q = rintf(x * inv_s);
     const float e = __builtin_fmaf(-q, s, x);
     const float h = 0.5f * s;
     const float ae = fabsf(e);
     const bool odd = ((int)q & 1) != 0;
     if (ae > h || (ae == h && odd)) q += e > 0.f ? 1.f : -1.f;
-    q = fminf(fmaxf(q, -(float)qmax), (float)qmax);
+    q = fminf(fmaxf(q, -(float)kQmax), (float)kQmax);
     return (int)q;
-}
-__device__ __forceinline__ int quant_code(float x, float s, float inv_s) {
-    return quant_code_max(x, s, inv_s, kQmax);
 }
 
 // --------------------------------------------------- W4A8 activation codes --
@@ -173,11 +168,6 @@ __device__ __forceinline__ u16x2 chunk_absmax2(const uint4 v) {
     return __builtin_elementwise_max(__builtin_elementwise_max(abs_bits2(v.x), abs_bits2(v.y)),
                                      __builtin_elementwise_max(abs_bits2(v.z), abs_bits2(v.w)));
 }
-__device__ __forceinline__ uint32_t chunk_absmax_bits(const uint4 v) {
-    const u16x2 m = chunk_absmax2(v);
-    return m.x > m.y ? m.x : m.y;
-}
-// the same over two 16-byte loads (16 fp16)
 __device__ __forceinline__ uint32_t chunk_absmax_bits(const uint4 v0, const uint4 v1) {
     const u16x2 m = __builtin_elementwise_max(chunk_absmax2(v0), chunk_absmax2(v1));
     return m.x > m.y ? m.x : m.y;
@@ -330,10 +320,6 @@ __device__ __forceinline__ i32x8 act_operand(const uint4 m, const uint2 t) {
 
 __device__ __forceinline__ uint4 ldg16(const uint8_t* p) {
     return *reinterpret_cast<const uint4*>(p);
-}
-
-__device__ __forceinline__ uint16_t ldg_u16(const void* base, int64_t idx) {
-    return reinterpret_cast<const uint16_t*>(base)[idx];
 }
 
 }  // namespace mq

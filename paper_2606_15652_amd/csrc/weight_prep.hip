@@ -13,8 +13,6 @@
 // 69 us.)
 #include "mq_device.h"
 
-#include <float.h>
-
 namespace mq {
 
 constexpr int kPrepThreads = 256;
