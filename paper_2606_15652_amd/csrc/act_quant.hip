@@ -68,10 +68,11 @@ __global__ __launch_bounds__(kActMaxThreads) void act_quant_kernel(
     float inv_s = s == 0.0f ? 0.0f : 1.0f / s;              // a zero scale: all codes 0
     if (t == 0) s_x[m] = sb;
     const bool finite = amax < kHalfInf;
-    if (!finite) nonfinite_scale<A8>(s, inv_s);
+    const uint32_t keep = finite ? ~0u : 0u;                // INT4: a row that is not finite has codes 0
+    if (A8 && __builtin_expect(!finite, 0)) s = inv_s = 1.0f;
 
     auto store = [&](Halves<C>& x, int c) {
-        if (!finite) nonfinite_values<A8>(x, amax);
+        if (A8 && __builtin_expect(!finite, 0)) x = nonfinite_values8(x, amax);
         float q[C];
         quant_codes(x, s, inv_s, (float)qmax, q);
         const int g = c / (kGroup / C), j = c % (kGroup / C);   // piece j of group g
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(kActMaxThreads) void act_quant_kernel(
             else
                 *reinterpret_cast<uint2*>(lo) = l0;
         } else {
-            const u32x6 d = operand_dwords(q);
+            const u32x6 d = operand_dwords(q) & keep;
             uint8_t* main = Xq + act_main_offset(M, m, g);
             if constexpr (C == 32) {
                 *reinterpret_cast<uint4*>(main + 16 * j) = make_uint4(d[0], d[1], d[2], d[3]);

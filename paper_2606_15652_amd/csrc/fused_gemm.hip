@@ -968,7 +968,8 @@ struct StreamDepth {
 // takes the low-plane MFMA and the fp8 x fp6 MFMA of the high plane chained
 // on its result (both exact), the rest is unchanged.
 template <int WM, int WN, int WGM, int WGN, bool RAW, int FQ, bool A8 = false, bool XS = false, bool PT = false>
-__global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs a) {
+__global__ __launch_bounds__(64 * kDecodeWaves, FQ ? 4 : 1)   // FQ: two workgroups a CU (one: 8192 -> 28672 at M = 4 28.1 -> 30.9 us)
+void gemm_stream_kernel(GemmArgs a) {
     static_assert(WN * WGN == 1 || WN * WGN == 2 || WN * WGN == 4 || WN * WGN == 8,
                   "tile columns inside one block row");
     static_assert(!(FQ && RAW), "fused quantisation feeds the fp16 path");
@@ -1352,15 +1353,11 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm_stream_kernel(GemmArgs
             const int g = c / (kGroup / kFC), e0 = c % (kGroup / kFC) * kFC, j = e0 >> 5;   // codes e0 .. of group g, quarter j
             if (m < M) {
                 const uint32_t amax = amax_sh[m];
-                float s = half_bits_to_float(scale_bits_from_amax(half_bits_to_float((uint16_t)amax)));
-                float inv_s = s == 0.0f ? 0.0f : 1.0f / s;
-                if (amax >= kHalfInf) {
-                    nonfinite_scale<false>(s, inv_s);
-                    nonfinite_values<false>(xv[i], amax);
-                }
+                const float s = half_bits_to_float(scale_bits_from_amax(half_bits_to_float((uint16_t)amax)));
                 float q[kFC];
-                quant_codes(xv[i], s, inv_s, (float)kQmax, q);
-                const u32x6 d = operand_dwords(q);
+                quant_codes(xv[i], s, s == 0.0f ? 0.0f : 1.0f / s, (float)kQmax, q);
+                u32x6 d = operand_dwords(q);
+                if (__builtin_expect(amax >= kHalfInf, 0)) d = u32x6{0u, 0u, 0u, 0u, 0u, 0u};   // not finite: codes 0
                 uint8_t* main = &xs[xs_main(g, m, j)];
                 uint8_t* tail = &xs[(uint32_t)G * (uint32_t)M * 64u + ((uint32_t)g * (uint32_t)M + (uint32_t)m) * 32u + (uint32_t)j * 8u];
                 if constexpr (FQ == 32) {

@@ -238,23 +238,20 @@ __device__ __forceinline__ void quant_codes(const Halves<C>& x, float s, float i
 }
 
 // A row whose largest |x| (its fp16 bits, amax) is infinite or NaN: its scale is
-// that value, and no quotient is a code.  INT4: all codes are 0 (so the outputs
-// are NaN, infinity times an exact zero).  INT8: 0 for the finite values beside
-// an infinity, -127 for the others and throughout a row with a NaN.  x is
-// replaced by values that the steps of quant_codes take to these codes with
-// the scale of nonfinite_scale.
+// that value, and no quotient is a code (quant_codes takes NaN to -qmax).
+// INT4: all codes are 0 (so the outputs are NaN, infinity times an exact zero);
+// the callers clear the operand dwords.  INT8: 0 for the finite values beside an
+// infinity, -127 for the others and throughout a row with a NaN: x is replaced
+// by 0 and NaN, with any finite scale.
 constexpr uint32_t kHalfInf = 0x7C00u;
-template <bool A8>
-__device__ __forceinline__ void nonfinite_scale(float& s, float& inv_s) {
-    s = A8 ? 0x1p-7f : 0.0f;
-    inv_s = A8 ? 0x1p7f : 0.0f;                            // -1 is clamped to -127
-}
-template <bool A8, int C>
-__device__ __forceinline__ void nonfinite_values(Halves<C>& x, uint32_t amax) {
-    auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0xBC00u : 0u; };
-    auto two = [&](uint32_t w) { return A8 ? one(w & 0xFFFFu) | (one(w >> 16) << 16) : 0u; };
+template <int C>
+__device__ __forceinline__ Halves<C> nonfinite_values8(const Halves<C>& x, uint32_t amax) {
+    auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0x7E00u : 0u; };
+    auto two = [&](uint32_t w) { return one(w & 0xFFFFu) | (one(w >> 16) << 16); };
+    Halves<C> y;
 #pragma unroll
-    for (int i = 0; i < C / 8; ++i) x.v[i] = make_uint4(two(x.v[i].x), two(x.v[i].y), two(x.v[i].z), two(x.v[i].w));
+    for (int i = 0; i < C / 8; ++i) y.v[i] = make_uint4(two(x.v[i].x), two(x.v[i].y), two(x.v[i].z), two(x.v[i].w));
+    return y;
 }
 
 // 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
