@@ -238,15 +238,15 @@ __device__ __forceinline__ void quant_codes(const Halves<C>& x, float s, float i
 }
 
 // A row whose largest |x| (its fp16 bits, amax) is infinite or NaN: its scale is
-// that value, and no quotient is a code (quant_codes takes NaN to -qmax).
+// that value, and no quotient is a code.
 // INT4: all codes are 0 (so the outputs are NaN, infinity times an exact zero);
 // the callers clear the operand dwords.  INT8: 0 for the finite values beside an
 // infinity, -127 for the others and throughout a row with a NaN: x is replaced
-// by 0 and NaN, with any finite scale.
+// by 0 and -128, with a scale of 1.
 constexpr uint32_t kHalfInf = 0x7C00u;
 template <int C>
 __device__ __forceinline__ Halves<C> nonfinite_values8(const Halves<C>& x, uint32_t amax) {
-    auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0x7E00u : 0u; };
+    auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0xD800u : 0u; };
     auto two = [&](uint32_t w) { return one(w & 0xFFFFu) | (one(w >> 16) << 16); };
     Halves<C> y;
 #pragma unroll
