@@ -98,13 +98,17 @@ typedef enum mq_variant {
     MQ_VARIANT_TILED = 2,    /* prefill: 128 x 128 output tiles, K-loop of groups */
     MQ_VARIANT_TILED_LARGE = 3, /* prefill: 256 x 256 output tiles (192 or 128
                                    rows where those fill the rounds better;
-                                   N % 256 == 0, else as TILED); AUTO takes it when
-                                   128 x 128 tiles would need more than one
-                                   round of two per CU                       */
+                                   N % 256 == 0, else as TILED); AUTO takes it
+                                   where its tiles' estimated time, over the
+                                   three heights and the short last tile row,
+                                   is below that of the 128 x 128 tiles'
+                                   rounds of two per CU (mq_fused_gemm_plan,
+                                   mq_fused_gemm_tile say which)             */
     MQ_VARIANT_MEDIUM = 4       /* 32 or 64 x 64 output tiles; AUTO takes it
                                    when 128 x 128 tiles would be too few to
                                    fill the chip and the 64 x 64 tiles fit in
-                                   one round (or in five, up to K = 8192)    */
+                                   one round (in four up to K = 4096, three
+                                   and a half up to K = 8192)                */
 } mq_variant;
 
 /* Static string naming a status code.  Never NULL. */
@@ -214,10 +218,10 @@ mq_status mq_fused_gemm_acc_i32(mq_variant variant, int M, int N, int K,
  * The whole layer from fp16 activations: mq_quantize_act followed by
  * mq_fused_gemm, with the same results bit for bit (Section 4.2 "Kernel
  * Fusion": quantisation fused into the GEMM).  For decode-sized inputs
- * (M <= 4 and M * K <= 32768, or
- * M <= 8 and M * K <= 24576, 16384 beyond N = 4096) one kernel does both: every workgroup quantises the
- * activation rows into LDS itself, which saves a launch.  Otherwise the
- * activations are quantised into the workspace first.
+ * (M <= 4 and M * K <= 32768, or M <= 8 and M * K <= 24576, 16384 beyond
+ * N = 4096) one kernel does both: every workgroup quantises the activation
+ * rows into LDS itself, which saves a launch.  Otherwise the activations are
+ * quantised into the workspace first.
  *   X, ldx   : fp16 [M, ldx], ldx >= K, ldx % 8 == 0, 16-byte aligned.
  *   others   : as for mq_fused_gemm.
  *   workspace: >= mq_linear_workspace_size(M, N, K) bytes, 16-byte aligned
