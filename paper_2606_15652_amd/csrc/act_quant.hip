@@ -64,15 +64,12 @@ __global__ __launch_bounds__(kActMaxThreads) void act_quant_kernel(
 
     constexpr int qmax = A8 ? kQmax8 : kQmax;
     const uint16_t sb = scale_bits_from_amax(half_bits_to_float((uint16_t)amax), qmax);
-    float s = half_bits_to_float(sb);
-    float inv_s = s == 0.0f ? 0.0f : 1.0f / s;              // a zero scale: all codes 0
+    const float s = A8 && sb == kHalfInf ? 0.0f : half_bits_to_float(sb);
+    const float inv_s = s == 0.0f ? 0.0f : 1.0f / s;        // a zero scale: all codes 0
     if (t == 0) s_x[m] = sb;
-    const bool finite = amax < kHalfInf;
-    const uint32_t keep = finite ? ~0u : 0u;                // INT4: a row that is not finite has codes 0
-    if (A8 && __builtin_expect(!finite, 0)) s = inv_s = 1.0f;
+    const uint32_t keep = amax < kHalfInf ? ~0u : 0u;       // INT4: a row that is not finite has codes 0
 
-    auto store = [&](Halves<C>& x, int c) {
-        if (A8 && __builtin_expect(!finite, 0)) x = nonfinite_values8(x, amax);
+    auto store = [&](const Halves<C>& x, int c) {
         float q[C];
         quant_codes(x, s, inv_s, (float)qmax, q);
         const int g = c / (kGroup / C), j = c % (kGroup / C);   // piece j of group g

@@ -237,22 +237,13 @@ __device__ __forceinline__ void quant_codes(const Halves<C>& x, float s, float i
     }
 }
 
-// A row whose largest |x| (its fp16 bits, amax) is infinite or NaN: its scale is
-// that value, and no quotient is a code.
-// INT4: all codes are 0 (so the outputs are NaN, infinity times an exact zero);
-// the callers clear the operand dwords.  INT8: 0 for the finite values beside an
-// infinity, -127 for the others and throughout a row with a NaN: x is replaced
-// by 0 and -128, with a scale of 1.
+// A row whose largest |x| (its fp16 bits) is infinite or NaN: its scale is that
+// value, and no quotient is a code.  INT4: all codes are 0 (so the outputs are
+// NaN, infinity times an exact zero); the callers clear the operand dwords.
+// INT8: 0 for the finite values beside an infinity, -127 for the others and
+// throughout a row with a NaN: quant_codes gives these with s = 0 in place of the
+// infinite scale (0 or NaN; the median of NaN and the two limits is the lower).
 constexpr uint32_t kHalfInf = 0x7C00u;
-template <int C>
-__device__ __forceinline__ Halves<C> nonfinite_values8(const Halves<C>& x, uint32_t amax) {
-    auto one = [&](uint32_t h) { return amax > kHalfInf || (h & kHalfInf) == kHalfInf ? 0xD800u : 0u; };
-    auto two = [&](uint32_t w) { return one(w & 0xFFFFu) | (one(w >> 16) << 16); };
-    Halves<C> y;
-#pragma unroll
-    for (int i = 0; i < C / 8; ++i) y.v[i] = make_uint4(two(x.v[i].x), two(x.v[i].y), two(x.v[i].z), two(x.v[i].w));
-    return y;
-}
 
 // 32 codes in [-7, 7] -> their six operand dwords (e2m3 fields q / 8, code e at
 // bit 6e; the instruction takes the even codes and the odd ones); 16 codes ->
