@@ -15,7 +15,7 @@
 // their operand dwords.  Few rows are bound by latency.  (256 threads of up
 // to 16 chunks of 16 codes, packed with integer operations, against this: INT4
 // 4096 x 4096 10.8 -> 9.6 us, 8192 x 8192 34.0 -> 28.8; INT8 2048 x 4096
-// 11.0 -> 7.0, 16 x 14336 10.8 -> 4.0.)
+// 11.0 -> 7.0, 16 x 14336 10.8 -> 3.9.)
 #include "mq_device.h"
 
 namespace mq {
